@@ -34,8 +34,12 @@
  *   - Outputs must not overlap any input or each other (MT_ERR_ALIAS).
  *   - Results are deterministic: no floating-point atomics are used, so the
  *     same call on the same inputs returns bit-identical outputs.
- *   - Floating point: fp32 operands are multiplied and accumulated in fp32
- *     (matrix cores, v_mfma_f32_32x32x2_f32). bf16 operands are multiplied
+ *   - Floating point: products of fp32 operands are summed in fp32; larger
+ *     ones run on the bf16 matrix cores with every value split exactly into
+ *     three bf16 parts (six v_mfma_f32_32x32x16_bf16 per 16 terms; measured
+ *     nearer the exact sums than fp32 instructions), falling back to
+ *     v_mfma_f32_32x32x2_f32 for tiles the split does not serve (infinities,
+ *     NaN, values next to the largest float, rows of tiny values). bf16 operands are multiplied
  *     exactly and accumulated in fp32 (v_mfma_f32_32x32x16_bf16). Every
  *     output, bias and bias gradient is fp32.
  */
@@ -376,11 +380,12 @@ mt_status mt_matmul_shape(int32_t na, const int64_t* a, int32_t nb, const int64_
  * those calls see it is unspecified; a production caller leaves them at
  * their defaults). Returns 0 = accepted, -1 = unknown key, -2 = value out of
  * range. Keys: "cfg" GEMM tile
- * configuration (-1 = automatic; register-staged tiles 0 = 256x256,
+ * configuration (-1 = automatic; fp32 runs 0-3 and 5 on the ring tiles of the
+ * same size; register-staged tiles 0 = 256x256,
  * 1 = 256x128, 2 = 128x256, 3 = 128x128, 4 = 64x64, 5 = 256x256 with 8 waves;
- * tiles streamed straight into an LDS ring 6 = 256x256 with 8 waves,
+ * tiles streamed straight into an LDS ring 6 = 256x256 (bf16: 8 waves),
  * 7 = 256x256 with 4 waves, 8 = 256x128, 9 = 128x256, 10 = 128x128,
- * 11 = 128x128 with 8 waves, 12 = 128x128 with 8 waves and 64-deep fp32
+ * 11 = 128x128 with 8 waves (bf16; fp32 as 10), 12 = 128x128 with 64-deep fp32
  * K-stages (bf16 maps it to 10), 13 = 256x192, 14 = 256x96 (K-contiguous B
  * only, else 8), 15 = 64x384 (13-15: fp32 operands without 16-byte aligned
  * rows only, else 8; bf16 10); fp32 operands that do not allow 16-byte loads

@@ -27,6 +27,16 @@ __device__ __forceinline__ float act_apply_t(float z) {
   else return z;
 }
 
+__device__ __forceinline__ float act_apply(int act, float z) {
+  switch (act) {
+    case kActRelu: return act_apply_t<kActRelu>(z);
+    case kActSigmoid: return act_apply_t<kActSigmoid>(z);
+    case kActTanh: return act_apply_t<kActTanh>(z);
+    case kActGelu: return act_apply_t<kActGelu>(z);
+    default: return z;
+  }
+}
+
 __device__ __forceinline__ float act_grad(int act, float z) {
   switch (act) {
     case kActRelu: return z > 0.f ? 1.f : 0.f;

@@ -357,75 +357,187 @@ struct ConvGatherB {
 template <typename T, bool A_KC, bool B_KC, int TM, int TN, int BK, int BM, int BN>
 struct DmaMma;
 
-// fp32: a k-step is a group of 8 k; within it, MFMA step j (0..3) takes
-// k = 8g + 4h + j for lane half h (one 16-byte read of a K-contiguous tile
-// feeds 4 steps).
+// fp32 products on the bf16 matrix cores, "X6". Every fp32 value is the sum of
+// three bf16 values of 8 significand bits each, x = h + m + l (h = x rounded
+// to bf16, m and l the same of what is left; exact down to 2^-134), so
+//   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + terms below 2^-24 |a b|,
+// six v_mfma_f32_32x32x16_bf16 per 16 k, exact products summed in fp32, small
+// terms first. An accumulator is rounded 6 times per 16 k where the fp32
+// instructions round it 16 times, so the sums are nearer the exact ones:
+// measured against 64 bits on normal data, K = 64 / 1024 / 8192: 1.06e-7 /
+// 4.95e-7 / 1.43e-6 relative, the fp32 instructions 1.39e-7 / 5.79e-7 / 1.62e-6.
+// 6 x 32 cycles against 8 x 64 for the same 16 k of a tile pair.
+// These instructions lose about 2^-9 of the accumulator's last place towards
+// minus infinity each: nothing within a run, but the runs of a long split
+// contraction would add it up (K = 100352 in 28 runs: 1.35e-6 where the fp32
+// instructions are 1.08e-6 off). TN products (weight gradients, the long
+// contractions) therefore negate B in every other run, and the runs' losses
+// cancel (0.95e-6).
+//
+// Not every input may be split: an infinite or NaN value gives NaN parts, one
+// within 2^-9 of the largest float rounds to an infinite h, and a row whose
+// values are all tiny loses its l (bf16 ends at 2^-133). The block therefore
+// checks its accumulators (every one finite) and that each row of A and
+// column of B is zero or holds a value of at least 2^-95 (parts lost below
+// 2^-126 are then under 2^-31 of it), and where either fails computes the
+// tile again with the fp32 instructions (plain_tile). The second check is the
+// OR of the h planes' bits: exponents below 32 leave the exponent's top three
+// bits clear, and one v_or3 takes four values.
 template <bool A_KC, bool B_KC, int TM, int TN, int BK, int BM, int BN>
 struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
-  static constexpr int KSTEPS = BK / 8;
-  struct Frags {
-    float a[4][TM], b[4][TN];
-  };
-  template <bool KC, int BMN, int N>
-  static __device__ __forceinline__ void frag(const char* S, int mn0, int g, int lane,
-                                              float (&f)[4][N], int i) {
-    using Tl = DmaTile<4, KC, BMN, BK>;
-    const int h = lane >> 5, mn = mn0 + (lane & 31);
-    if constexpr (KC) {
-      const f32x4 v = *(const f32x4*)(S + Tl::addr(mn, 8 * g + 4 * h));
-      f[0][i] = v[0];
-      f[1][i] = v[1];
-      f[2][i] = v[2];
-      f[3][i] = v[3];
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) f[j][i] = *(const float*)(S + Tl::addr(8 * g + 4 * h + j, mn));
-    }
-  }
+  static constexpr int KSTEPS = BK / 16;
+  static_assert(BK % 16 == 0, "k-steps of 16");
+  static constexpr int CHUNKS = TM;  // chunk i: row i of the wave's tiles
   // An M-contiguous A (TN products) is read TM consecutive rows at a time:
   // tile i's row r is the wave's row TM r + i (ROW_PERM), so one TM-wide read
   // of LDS row k feeds all TM tiles instead of TM 4-byte reads; the epilogue
   // writes tile i's row r to that row.
   static constexpr bool ROW_PERM = !A_KC && (TM == 2 || TM == 4);
   typedef float f32xTM __attribute__((ext_vector_type(TM == 4 ? 4 : 2)));
-  static __device__ __forceinline__ void load(const char* As, const char* Bs, int am, int bn,
-                                              int lane, int g, Frags& f) {
-    if constexpr (ROW_PERM) {
-      using Tl = DmaTile<4, false, BM, BK>;
-      const int h = lane >> 5, c = am + TM * (lane & 31);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32xTM v = *(const f32xTM*)(As + Tl::addr(8 * g + 4 * h + j, c));
-#pragma unroll
-        for (int i = 0; i < TM; ++i) f.a[j][i] = v[i];
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) frag<A_KC, BM, TM>(As, am + i * 32, g, lane, f.a, i);
-    }
-#pragma unroll
-    for (int i = 0; i < TN; ++i) frag<B_KC, BN, TN>(Bs, bn + i * 32, g, lane, f.b, i);
-  }
-  // Column sums of an M-contiguous A over the k-step's 4 MFMA steps: tile
-  // i's value goes to the lane's column (see a_col), lane half h holding k
-  // = 8g + 4h + j.
-  static __device__ __forceinline__ void colsum(const Frags& f, float (&cs)[TM]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) cs[i] += (f.a[0][i] + f.a[1][i]) + (f.a[2][i] + f.a[3][i]);
-  }
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  struct Planes {
+    bf16x8 h, m, l;
+  };
+  // the lane's 8 k of each tile: 16 ks + 8 u + 4 (lane half) + j for element
+  // 4 u + j (the k order within a k-step is free as long as A and B agree;
+  // this one keeps the LDS reads of the fp32 form)
+  struct Frags {
+    float a[TM][8], b[TN][8];
+  };
   // the column of A (from the wave's first) whose values tile i holds in this lane
   static __device__ __forceinline__ int a_col(int lane, int i) {
     return ROW_PERM ? TM * (lane & 31) + i : 32 * i + (lane & 31);
   }
-  // a k-step's MFMAs in 4 chunks: chunk j is MFMA step j of every tile
-  static constexpr int CHUNKS = 4;
-  static __device__ __forceinline__ void compute_chunk(const Frags& f, f32x16 (&acc)[TM][TN],
-                                                       int j) {
+  template <bool KC, int BMN>
+  static __device__ __forceinline__ void frag(const char* S, int mn0, int ks, int lane, float (&f)[8]) {
+    using Tl = DmaTile<4, KC, BMN, BK>;
+    const int h = lane >> 5, mn = mn0 + (lane & 31);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int k0 = 16 * ks + 8 * u + 4 * h;
+      if constexpr (KC) {
+        const f32x4 v = *(const f32x4*)(S + Tl::addr(mn, k0));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[4 * u + j] = v[j];
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[4 * u + j] = *(const float*)(S + Tl::addr(k0 + j, mn));
+      }
+    }
+  }
+  static __device__ __forceinline__ void load_b(const char* Bs, int bn, int lane, int ks, Frags& f) {
+#pragma unroll
+    for (int i = 0; i < TN; ++i) frag<B_KC, BN>(Bs, bn + i * 32, ks, lane, f.b[i]);
+  }
+  // A tile i (row-permuted A, whose reads serve every tile at once: all of
+  // them with the last tile)
+  static __device__ __forceinline__ void load_a(const char* As, int am, int lane, int ks, Frags& f, int i) {
+    if constexpr (ROW_PERM) {
+      if (i != TM - 1) return;
+      using Tl = DmaTile<4, false, BM, BK>;
+      const int h = lane >> 5, c = am + TM * (lane & 31);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const f32xTM v = *(const f32xTM*)(As + Tl::addr(16 * ks + 8 * (e >> 2) + 4 * h + (e & 3), c));
+#pragma unroll
+        for (int t = 0; t < TM; ++t) f.a[t][e] = v[t];
+      }
+    } else {
+      frag<A_KC, BM>(As, am + i * 32, ks, lane, f.a[i]);
+    }
+  }
+  // sign: 0, or the sign bit to split -x
+  static __device__ __forceinline__ Planes split(const float (&x)[8], uint32_t sign) {
+    float y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = __uint_as_float(__float_as_uint(x[e]) ^ sign);
+    return split(y);
+  }
+  static __device__ __forceinline__ Planes split(const float (&x)[8]) {
+    // x - h as one v_dot2_f32_bf16 per value, h's register and its neighbour's
+    // against (-1, 0) or (0, -1): 7 instructions a pair where taking the
+    // halves apart and subtracting takes 11 (8192^3: 4.90 against 4.93 ms, and
+    // less power). Opaque: as an immediate the compiler would take the pair
+    // for the inline constant -1.0, which the instruction reads as (0, -1).
+    uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;
+    __asm__("" : "+s"(c0), "+s"(c1));
+    const bf16x2 n0 = __builtin_bit_cast(bf16x2, c0), n1 = __builtin_bit_cast(bf16x2, c1);
+    Planes p;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      const f32x2 v = {x[e], x[e + 1]};
+      const bf16x2 h = __builtin_convertvector(v, bf16x2);  // v_cvt_pk_bf16_f32, nearest even
+      const f32x2 r = {__builtin_amdgcn_fdot2_f32_bf16(h, n0, v[0], false),
+                       __builtin_amdgcn_fdot2_f32_bf16(h, n1, v[1], false)};
+      const bf16x2 m = __builtin_convertvector(r, bf16x2);
+      const f32x2 q = {__builtin_amdgcn_fdot2_f32_bf16(m, n0, r[0], false),
+                       __builtin_amdgcn_fdot2_f32_bf16(m, n1, r[1], false)};
+      const bf16x2 l = __builtin_convertvector(q, bf16x2);
+      p.h[e] = h[0];
+      p.h[e + 1] = h[1];
+      p.m[e] = m[0];
+      p.m[e + 1] = m[1];
+      p.l[e] = l[0];
+      p.l[e + 1] = l[1];
+    }
+    return p;
+  }
+  // one row of the wave's tiles over the k-step
+  static __device__ __forceinline__ void mfma(const Planes& a, const Planes (&b)[TN], f32x16 (&acc)[TN]) {
+    auto step = [&](bf16x8 Planes::*pb, bf16x8 Planes::*pa) {
+#pragma unroll
+      for (int q = 0; q < TN; ++q)
+        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[q].*pb, a.*pa, acc[q], 0, 0, 0);
+    };
+    step(&Planes::l, &Planes::h);
+    step(&Planes::h, &Planes::l);
+    step(&Planes::m, &Planes::m);
+    step(&Planes::m, &Planes::h);
+    step(&Planes::h, &Planes::m);
+    step(&Planes::h, &Planes::h);
+  }
+  // column sums of an M-contiguous A over the k-step: tile i's value goes to
+  // the lane's column (a_col)
+  static __device__ __forceinline__ void colsum(const Frags& f, float (&cs)[TM]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+      cs[i] += ((f.a[i][0] + f.a[i][1]) + (f.a[i][2] + f.a[i][3])) +
+               ((f.a[i][4] + f.a[i][5]) + (f.a[i][6] + f.a[i][7]));
+  }
+  // the bits of a row's (column's) h planes, ORed
+  static __device__ __forceinline__ void note(const Planes& x, uint32_t& bits) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 h = __builtin_bit_cast(u32x4, x.h);
+    bits |= h[0] | h[1];
+    bits |= h[2] | h[3];
+  }
+  // whether any of the lane's rows holds only values too small to split; the
+  // bits start over
+  template <int N>
+  static __device__ __forceinline__ bool any_tiny(uint32_t (&bits)[N]) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      uint32_t t = bits[i] | (uint32_t)__shfl_xor((int)bits[i], 32);
+      t |= t >> 16;
+      bad |= (t & 0x7fffu) != 0 && (t & 0x7000u) == 0;
+      bits[i] = 0;
+    }
+    return bad;
+  }
+  static __device__ __forceinline__ bool any_not_finite(const f32x16 (&acc)[TM][TN]) {
+    float z[4] = {0.f, 0.f, 0.f, 0.f};  // 0 x finite = 0, 0 x (inf or NaN) = NaN
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int q = 0; q < TN; ++q)
-        acc[i][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.b[j][q], f.a[j][i], acc[i][q], 0, 0, 0);
+      for (int q = 0; q < TN; ++q) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) z[e & 3] = __builtin_fmaf(acc[i][q][e], 0.f, z[e & 3]);
+        __builtin_amdgcn_sched_barrier(0);  // a tile at a time: no more registers than that
+      }
+    const float t = (z[0] + z[1]) + (z[2] + z[3]);
+    return t != t;
   }
 };
 
@@ -569,7 +681,7 @@ void conv_dma_sk_kernel(const GemmParams p) {
   using T = float;
   constexpr bool A_KC = true, B_KC = CONV_ == 1, EPI = false, VEC_C = true, KTAIL = false;
   constexpr int DMA_G0 = 1, DMA_GS = 1, DMA_LANE = 16, CONV = CONV_;
-  constexpr bool SK = true;
+  constexpr bool SK = true, PERSIST = false;
   const int64_t ks_all = (p.K + BK - 1) / BK;
   const int64_t U = (int64_t)p.tiles_m * p.tiles_n * ks_all, G = gridDim.x;
   const int64_t u_end = ((int64_t)blockIdx.x + 1) * U / G;
@@ -580,7 +692,6 @@ void conv_dma_sk_kernel(const GemmParams p) {
     const SkSeg seg = sk_segment(sk_t, sk_ka, ks_all, G, U);
     const bool sk_part = seg.n > 1;
     const int sk_slot = seg.slot;
-  constexpr bool PERSIST = false;
 #include "gemm_dma_body.inc"
     u = sk_t * ks_all + sk_kb;
     __syncthreads();  // the next segment's loads reuse the ring

@@ -1,11 +1,26 @@
-// fp32 instantiations of the matrix-core GEMM (see gemm_kernel.hpp):
-// v_mfma_f32_32x32x2_f32, BK = 16, 16-byte (VEC = 4) or 4-byte (VEC = 1) loads.
+// Launches of the fp32 products: the DMA-ring tiles, whose products run on
+// the bf16 matrix cores (gemm_dma.hpp), and the register-staged 64x64 tile
+// (gemm_kernel.hpp, v_mfma_f32_32x32x2_f32).
+//
+// The file compiles whole, or one part at a time for a parallel build
+// (MT_F32_PART: 1 NT, 2 NN, 3 TN and TT, 4 the convolution's products, 5 the
+// dispatch; 0 or unset: all).
 #include "gemm_dma.hpp"
 #include "gemm_kernel.hpp"
 #include "kernels.hpp"
 
+#ifndef MT_F32_PART
+#define MT_F32_PART 0
+#endif
+#define MT_F32_HAS(n) (MT_F32_PART == 0 || MT_F32_PART == (n))
+
 namespace mt {
 
+hipError_t gemm_f32_nt(const GemmParams& p, bool vec, int cfg, hipStream_t stream);
+hipError_t gemm_f32_nn(const GemmParams& p, bool vec, int cfg, hipStream_t stream);
+hipError_t gemm_f32_tn(const GemmParams& p, bool b_kc, bool vec, int cfg, hipStream_t stream);
+
+#if MT_F32_HAS(1) || MT_F32_HAS(2) || MT_F32_HAS(3)
 template <bool A_KC, bool B_KC, int BM, int BN, int BK, int WGM, int WGN, int VEC, int WPE,
           bool EPI = false>
 static hipError_t launch_f32(const GemmParams& p, hipStream_t stream) {
@@ -48,17 +63,23 @@ static hipError_t launch_dma(const GemmParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <bool A_KC, bool B_KC, int VEC>
-static hipError_t launch_layout(const GemmParams& p, int cfg, hipStream_t stream) {
-  if constexpr (VEC == 1) {
-    // operands or output without 16-byte aligned rows: the DMA tiles with
-    // 4-byte lanes and element stores, or the element-load register-staged
-    // kernels up to 128x128 (larger tiles would spill staging registers)
+// The tile configurations (kernels.hpp). Every wave owns 64 to 128 rows and
+// columns of accumulators: the split of a value into its three parts is paid
+// once per wave that reads it, so the 4-wave tiles (128x128 a wave) beat the
+// 8-wave ones (128x64): 8192^3 NT 4.90 against 5.21 ms, 4096 x 1024 x 1024 on
+// 128x128 tiles 56.5 against 57.3 us.
+template <bool A_KC, bool B_KC>
+static hipError_t launch_layout(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
+  if (!vec) {
+    // operands or output without 16-byte aligned rows: 4-byte lanes and
+    // staged stores
     switch (cfg) {
-      case kCfgDma256x256: return launch_dma<A_KC, B_KC, 256, 256, 32, 2, 4, 2, 2, false, 4, false>(p, stream);
+      case kCfg256x256: case kCfg256x256x64w8: case kCfgDma256x256w4:
+      case kCfgDma256x256: return launch_dma<A_KC, B_KC, 256, 256, 32, 2, 2, 2, 1, false, 4, false>(p, stream);
+      case kCfg256x128:
       case kCfgDma256x128: return launch_dma<A_KC, B_KC, 256, 128, 16, 2, 2, 3, 2, false, 4, false>(p, stream);
+      case kCfg128x256:
       case kCfgDma128x256: return launch_dma<A_KC, B_KC, 128, 256, 16, 2, 2, 3, 2, false, 4, false>(p, stream);
-      case kCfgDma128x128: return launch_dma<A_KC, B_KC, 128, 128, 32, 2, 2, 2, 2, false, 4, false>(p, stream);
       case kCfgDma256x192: return launch_dma<A_KC, B_KC, 256, 192, 16, 4, 2, 4, 2, false, 4, false>(p, stream);
       case kCfgDma256x96:
         // an N-contiguous B would need 384-byte LDS rows, which the swizzle cannot serve
@@ -66,73 +87,56 @@ static hipError_t launch_layout(const GemmParams& p, int cfg, hipStream_t stream
         else return hipErrorInvalidValue;
       case kCfgDma64x384: return launch_dma<A_KC, B_KC, 64, 384, 16, 1, 4, 2, 2, false, 4, false>(p, stream);
       case kCfg64x64: return launch_f32<A_KC, B_KC, 64, 64, 16, 2, 2, 1, 4>(p, stream);
-      default: return launch_f32<A_KC, B_KC, 128, 128, 16, 2, 2, 1, 2>(p, stream);
-    }
-  } else {
-    switch (cfg) {
-      case kCfgDma256x256: return launch_dma<A_KC, B_KC, 256, 256, 32, 2, 4, 2, 2>(p, stream);
-      case kCfgDma256x256w4: return launch_dma<A_KC, B_KC, 256, 256, 32, 2, 2, 2, 1>(p, stream);
-      case kCfgDma256x128: return launch_dma<A_KC, B_KC, 256, 128, 16, 2, 2, 3, 2>(p, stream);
-      case kCfgDma128x256: return launch_dma<A_KC, B_KC, 128, 256, 16, 2, 2, 3, 2>(p, stream);
-      case kCfgDma128x128: return launch_dma<A_KC, B_KC, 128, 128, 32, 2, 2, 2, 2>(p, stream);
-      case kCfgDma128x128w8: return launch_dma<A_KC, B_KC, 128, 128, 32, 2, 4, 2, 4>(p, stream);
-      case kCfgDma128x128k64: return launch_dma<A_KC, B_KC, 128, 128, 64, 2, 4, 2, 2>(p, stream);
-      case kCfg256x256: return launch_f32<A_KC, B_KC, 256, 256, 16, 2, 2, VEC, 1>(p, stream);
-      case kCfg256x256x64w8: return launch_f32<A_KC, B_KC, 256, 256, 32, 2, 4, VEC, 2>(p, stream);
-      case kCfg256x128: return launch_f32<A_KC, B_KC, 256, 128, 16, 2, 2, VEC, 2>(p, stream);
-      case kCfg128x256: return launch_f32<A_KC, B_KC, 128, 256, 16, 2, 2, VEC, 2>(p, stream);
-      case kCfg128x128: return launch_f32<A_KC, B_KC, 128, 128, 16, 2, 2, VEC, 2>(p, stream);
-      default: return launch_f32<A_KC, B_KC, 64, 64, 16, 2, 2, VEC, 4>(p, stream);
+      default: return launch_dma<A_KC, B_KC, 128, 128, 32, 2, 2, 2, 2, false, 4, false>(p, stream);
     }
   }
-}
-
-int gemm_tile_m(int cfg) {
   switch (cfg) {
-    case kCfg256x256: case kCfg256x128: case kCfg256x256x64w8: case kCfgDma256x256:
-    case kCfgDma256x256w4: case kCfgDma256x128: case kCfgDma256x192: case kCfgDma256x96: return 256;
-    case kCfg128x256: case kCfg128x128: case kCfgDma128x256: case kCfgDma128x128:
-    case kCfgDma128x128w8: case kCfgDma128x128k64: return 128;
-    default: return 64;
+    case kCfg256x256: case kCfg256x256x64w8: case kCfgDma256x256w4:
+    case kCfgDma256x256: return launch_dma<A_KC, B_KC, 256, 256, 32, 2, 2, 2, 1>(p, stream);
+    case kCfg256x128:
+    case kCfgDma256x128: return launch_dma<A_KC, B_KC, 256, 128, 16, 2, 2, 3, 2>(p, stream);
+    case kCfg128x256:
+    case kCfgDma128x256: return launch_dma<A_KC, B_KC, 128, 256, 16, 2, 2, 3, 2>(p, stream);
+    case kCfgDma128x128k64: return launch_dma<A_KC, B_KC, 128, 128, 64, 2, 2, 2, 1>(p, stream);
+    case kCfg64x64: return launch_f32<A_KC, B_KC, 64, 64, 16, 2, 2, 4, 4>(p, stream);
+    default: return launch_dma<A_KC, B_KC, 128, 128, 32, 2, 2, 2, 2>(p, stream);
   }
 }
-int gemm_tile_n(int cfg) {
-  switch (cfg) {
-    case kCfg256x256: case kCfg128x256: case kCfg256x256x64w8: case kCfgDma256x256:
-    case kCfgDma256x256w4: case kCfgDma128x256: return 256;
-    case kCfg256x128: case kCfg128x128: case kCfgDma256x128: case kCfgDma128x128:
-    case kCfgDma128x128w8: case kCfgDma128x128k64: return 128;
-    case kCfgDma256x192: return 192;
-    case kCfgDma256x96: return 96;
-    case kCfgDma64x384: return 384;
-    default: return 64;
-  }
-}
-int gemm_tile_k(int cfg, bool bf16) {
-  if (cfg == kCfgDma128x128k64) return 64;
-  if (cfg == kCfg256x256x64w8) return bf16 ? 64 : 32;
-  if (cfg == kCfgDma256x256 || cfg == kCfgDma256x256w4 || cfg == kCfgDma128x128 ||
-      cfg == kCfgDma128x128w8)
-    return bf16 ? 64 : 32;
-  return bf16 ? 32 : 16;
-}
+#endif
 
-// The dense layer followed by a nonlinearity (z / act set): the forward
-// layout only, on the 256x256 or 128x128 DMA tiles or the 128x128 / 64x64
-// register-staged tiles.
+#if MT_F32_HAS(1)
+// The dense layer followed by a nonlinearity (z / act set), on the 256x256 or
+// 128x128 DMA tiles or the 64x64 register-staged tile.
 static hipError_t launch_epi(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
-  if (vec) {
-    if (cfg == kCfgDma128x128)
-      return launch_dma<true, true, 128, 128, 32, 2, 2, 2, 2, true>(p, stream);
-    if (cfg == kCfgDma256x256)
-      return launch_dma<true, true, 256, 256, 32, 2, 4, 2, 2, true>(p, stream);
-    if (cfg == kCfg128x128) return launch_f32<true, true, 128, 128, 16, 2, 2, 4, 2, true>(p, stream);
-    return launch_f32<true, true, 64, 64, 16, 2, 2, 4, 4, true>(p, stream);
-  }
-  if (cfg == kCfg128x128) return launch_f32<true, true, 128, 128, 16, 2, 2, 1, 2, true>(p, stream);
-  return launch_f32<true, true, 64, 64, 16, 2, 2, 1, 4, true>(p, stream);
+  if (cfg == kCfg64x64)
+    return vec ? launch_f32<true, true, 64, 64, 16, 2, 2, 4, 4, true>(p, stream)
+               : launch_f32<true, true, 64, 64, 16, 2, 2, 1, 4, true>(p, stream);
+  if (!vec) return launch_dma<true, true, 128, 128, 32, 2, 2, 2, 2, true, 4, false>(p, stream);
+  if (cfg == kCfgDma256x256) return launch_dma<true, true, 256, 256, 32, 2, 2, 2, 1, true>(p, stream);
+  return launch_dma<true, true, 128, 128, 32, 2, 2, 2, 2, true>(p, stream);
 }
 
+hipError_t gemm_f32_nt(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
+  if (p.act || p.z) return launch_epi(p, vec, cfg, stream);
+  return launch_layout<true, true>(p, vec, cfg, stream);
+}
+#endif
+
+#if MT_F32_HAS(2)
+// K-contiguous A, N-contiguous B (dX = dY W)
+hipError_t gemm_f32_nn(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
+  return launch_layout<true, false>(p, vec, cfg, stream);
+}
+#endif
+
+#if MT_F32_HAS(3)
+// M-contiguous A (dW = dY^T X; TT with a K-contiguous B)
+hipError_t gemm_f32_tn(const GemmParams& p, bool b_kc, bool vec, int cfg, hipStream_t stream) {
+  return b_kc ? launch_layout<false, true>(p, vec, cfg, stream) : launch_layout<false, false>(p, vec, cfg, stream);
+}
+#endif
+
+#if MT_F32_HAS(4)
 template <int MODE, int BM, int BN, int BK, int WGM, int WGN, int NS, int WPE>
 static hipError_t launch_conv(const GemmParams& p, hipStream_t stream) {
   GemmParams q = p;
@@ -157,9 +161,9 @@ static hipError_t launch_conv(const GemmParams& p, hipStream_t stream) {
 template <int MODE>
 static hipError_t conv_cfg(const GemmParams& p, int cfg, hipStream_t stream) {
   switch (cfg) {
-    case kCfgDma256x256: return launch_conv<MODE, 256, 256, 32, 2, 4, 2, 2>(p, stream);
-    case kCfgDma128x128: return launch_conv<MODE, 128, 128, 32, 2, 2, 2, 2>(p, stream);
-    case kCfgDma128x128w8: return launch_conv<MODE, 128, 128, 32, 2, 4, 2, 4>(p, stream);
+    case kCfgDma256x256: return launch_conv<MODE, 256, 256, 32, 2, 2, 2, 1>(p, stream);
+    case kCfgDma128x128:
+    case kCfgDma128x128w8: return launch_conv<MODE, 128, 128, 32, 2, 2, 2, 2>(p, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -215,11 +219,11 @@ hipError_t gemm_f32_conv_sk(const GemmParams& p, int mode, int blocks, hipStream
   if (p.M <= 0 || p.N <= 0 || blocks <= 0 || p.K % 32 != 0 || p.N % 4 != 0)
     return hipErrorInvalidValue;
   if (mode == 1)
-    hipLaunchKernelGGL((gemm::conv_dma_sk_kernel<1, 256, 256, 32, 2, 4, 2, 2>), dim3(blocks),
-                       dim3(512), 0, stream, q);
+    hipLaunchKernelGGL((gemm::conv_dma_sk_kernel<1, 256, 256, 32, 2, 2, 2, 1>), dim3(blocks),
+                       dim3(256), 0, stream, q);
   else if (mode == 3)
-    hipLaunchKernelGGL((gemm::conv_dma_sk_kernel<3, 256, 256, 32, 2, 4, 2, 2>), dim3(blocks),
-                       dim3(512), 0, stream, q);
+    hipLaunchKernelGGL((gemm::conv_dma_sk_kernel<3, 256, 256, 32, 2, 2, 2, 1>), dim3(blocks),
+                       dim3(256), 0, stream, q);
   else
     return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
@@ -248,8 +252,8 @@ hipError_t gemm_f32_conv_phases(const GemmParams& p, const ConvPhases& tab, hipS
   const int64_t blocks = tab.tile0[tab.n];
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((gemm::conv_dgrad_phases_kernel<256, 256, 32, 2, 4, 2, 2>), dim3((unsigned)blocks),
-                     dim3(512), 0, stream, q, tab);
+  hipLaunchKernelGGL((gemm::conv_dgrad_phases_kernel<256, 256, 32, 2, 2, 2, 1>), dim3((unsigned)blocks),
+                     dim3(256), 0, stream, q, tab);
   return hipGetLastError();
 }
 
@@ -274,23 +278,45 @@ hipError_t gemm_f32_conv(const GemmParams& p, int mode, int cfg, hipStream_t str
   if (mode == 4) return conv_cfg<4>(p, cfg, stream);
   return hipErrorInvalidValue;
 }
+#endif
+
+#if MT_F32_HAS(5)
+int gemm_tile_m(int cfg) {
+  switch (cfg) {
+    case kCfg256x256: case kCfg256x128: case kCfg256x256x64w8: case kCfgDma256x256:
+    case kCfgDma256x256w4: case kCfgDma256x128: case kCfgDma256x192: case kCfgDma256x96: return 256;
+    case kCfg128x256: case kCfg128x128: case kCfgDma128x256: case kCfgDma128x128:
+    case kCfgDma128x128w8: case kCfgDma128x128k64: return 128;
+    default: return 64;
+  }
+}
+int gemm_tile_n(int cfg) {
+  switch (cfg) {
+    case kCfg256x256: case kCfg128x256: case kCfg256x256x64w8: case kCfgDma256x256:
+    case kCfgDma256x256w4: case kCfgDma128x256: return 256;
+    case kCfg256x128: case kCfg128x128: case kCfgDma256x128: case kCfgDma128x128:
+    case kCfgDma128x128w8: case kCfgDma128x128k64: return 128;
+    case kCfgDma256x192: return 192;
+    case kCfgDma256x96: return 96;
+    case kCfgDma64x384: return 384;
+    default: return 64;
+  }
+}
+int gemm_tile_k(int cfg, bool bf16) {
+  if (cfg == kCfgDma128x128k64) return 64;
+  if (cfg == kCfg256x256x64w8) return bf16 ? 64 : 32;
+  if (cfg == kCfgDma256x256 || cfg == kCfgDma256x256w4 || cfg == kCfgDma128x128 ||
+      cfg == kCfgDma128x128w8)
+    return bf16 ? 64 : 32;
+  return bf16 ? 32 : 16;
+}
 
 hipError_t gemm_f32(const GemmParams& p, bool a_kc, bool b_kc, bool vec, int cfg,
                     hipStream_t stream) {
-  if (p.act || p.z) {
-    if (!a_kc || !b_kc) return hipErrorInvalidValue;
-    return launch_epi(p, vec, cfg, stream);
-  }
-  if (vec) {
-    if (a_kc && b_kc) return launch_layout<true, true, 4>(p, cfg, stream);
-    if (a_kc && !b_kc) return launch_layout<true, false, 4>(p, cfg, stream);
-    if (!a_kc && b_kc) return launch_layout<false, true, 4>(p, cfg, stream);
-    return launch_layout<false, false, 4>(p, cfg, stream);
-  }
-  if (a_kc && b_kc) return launch_layout<true, true, 1>(p, cfg, stream);
-  if (a_kc && !b_kc) return launch_layout<true, false, 1>(p, cfg, stream);
-  if (!a_kc && b_kc) return launch_layout<false, true, 1>(p, cfg, stream);
-  return launch_layout<false, false, 1>(p, cfg, stream);
+  if ((p.act || p.z) && !(a_kc && b_kc)) return hipErrorInvalidValue;
+  if (!a_kc) return gemm_f32_tn(p, b_kc, vec, cfg, stream);
+  return b_kc ? gemm_f32_nt(p, vec, cfg, stream) : gemm_f32_nn(p, vec, cfg, stream);
 }
+#endif
 
 }  // namespace mt

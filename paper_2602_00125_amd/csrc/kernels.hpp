@@ -9,9 +9,10 @@
 namespace mt {
 
 // GEMM tile configurations: register-staged tiles (BM x BN; BK = 16 fp32 /
-// 32 bf16; 4 waves per block), a register-staged 256x256 tile with 8 waves
-// and BK = 32 fp32 / 64 bf16, and tiles whose operands stream straight into
-// an LDS ring (gemm_dma.hpp).
+// 32 bf16; 4 waves per block; fp32 keeps only 64x64 of them and runs the
+// others on the ring tile of the same size), a register-staged 256x256 tile
+// with 8 waves and BK = 64 (bf16), and tiles whose operands stream straight
+// into an LDS ring (gemm_dma.hpp).
 enum GemmCfg {
   kCfg256x256 = 0,
   kCfg256x128 = 1,
@@ -19,13 +20,13 @@ enum GemmCfg {
   kCfg128x128 = 3,
   kCfg64x64 = 4,
   kCfg256x256x64w8 = 5,
-  kCfgDma256x256 = 6,    // 256x256, 8 waves, BK = 32 / 64, 2-stage ring (128 KB), 1 block per CU
+  kCfgDma256x256 = 6,    // 256x256, fp32 4 waves, bf16 8, BK = 32 / 64, 2-stage ring (128 KB), 1 block per CU
   kCfgDma256x256w4 = 7,  // the same with 4 waves (128x128 per wave)
   kCfgDma256x128 = 8,    // 256x128, 4 waves, BK = 16 / 32, 3-stage ring (72 KB), 2 blocks per CU
   kCfgDma128x256 = 9,    // 128x256, likewise
   kCfgDma128x128 = 10,   // 128x128, 4 waves, BK = 32 / 64, 2-stage ring (64 KB), 2 blocks per CU
-  kCfgDma128x128w8 = 11, // the same tile with 8 waves (fp32: 64x32 each; bf16: 32x64)
-  kCfgDma128x128k64 = 12, // fp32 only: 128x128, 8 waves of 64x32, BK = 64, 2-stage ring (128 KB), 1 block per CU
+  kCfgDma128x128w8 = 11, // the same tile with 8 waves of 32x64 (bf16; fp32 as 4 waves)
+  kCfgDma128x128k64 = 12, // fp32 only: 128x128, 4 waves, BK = 64, 2-stage ring (128 KB), 1 block per CU
   // fp32 operands without 16-byte aligned rows (4-byte lanes), tiles shaped
   // for dimensions just past a multiple of 128 or 256 (every wave 64x96):
   kCfgDma256x192 = 13,   // 8 waves, BK = 16, 4-stage ring (112 KB), 1 block per CU

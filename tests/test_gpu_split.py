@@ -1,0 +1,170 @@
+"""fp32 products on the bf16 matrix cores split every value in three bf16 parts.
+
+What the split does not serve (infinities, NaN, values near the largest float,
+rows of tiny values) must come out as in fp32 arithmetic, and what it serves
+must be no further from the exact sums than fp32 accumulation is.
+"""
+from __future__ import annotations
+
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2602_00125_amd import binding as b  # noqa: E402
+DEV = "cuda:0"
+# 256x256, 128x128 (two depths), 256x128, 128x256 with 16-byte lanes; with
+# vec1 those and 256x192, 256x96, 64x384 with 4-byte lanes
+CFGS = [(c, 0) for c in (6, 8, 9, 10, 12)] + [(c, 1) for c in (6, 8, 9, 10, 13, 14, 15)]
+KINDS = ["inf", "nan", "huge", "tiny_rows", "tiny_rows_big_other", "zero_rows"]
+
+
+def spoil(x, w, kind):
+    """Rows of x (and of w) of the kind; the rest stays as drawn."""
+    if kind == "inf":
+        x[37, 5], x[201, 7], w[3, 11] = math.inf, -math.inf, math.inf
+    elif kind == "nan":
+        x[130, 1] = math.nan
+    elif kind == "huge":  # h rounds to infinity; the products stay finite
+        x[64, 3], x[65, 4] = 3.4028e38, -3.4027e38
+        w *= 1e-6
+    elif kind == "tiny_rows":
+        x[10:20] *= 1e-36
+    elif kind == "tiny_rows_big_other":
+        x *= 1e-36
+        w *= 1e30
+    elif kind == "zero_rows":
+        x[5:9] = 0.0
+        w[2] = 0.0
+    return x, w
+
+
+def check(got, want, S, K, what):
+    """As fp32 sums of K products: |got - want| <= c S u, c = 2 sqrt(K) + 4
+    for roundings of random sign (u = 2^-24), and one tiny float for a result
+    in the subnormal range; not finite exactly where the exact result is not."""
+    got = got.double().cpu()
+    fin = torch.isfinite(want)
+    assert torch.equal(torch.isnan(got), torch.isnan(want)), what
+    assert torch.equal(got[~fin & ~torch.isnan(want)], want[~fin & ~torch.isnan(want)]), what
+    err = (got - want).abs()[fin]
+    bound = ((2 * math.sqrt(K) + 4) * 2.0 ** -24 * S + 2.0 ** -126)[fin]
+    assert bool((err <= bound).all()), f"{what}: {float((err / bound).max())}"
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("cfg,vec1", CFGS)
+def test_products_of_values_the_split_does_not_serve(cfg, vec1, kind):
+    M, N, K = 300, 200, 136
+    g = torch.Generator().manual_seed(cfg)
+    x, w = spoil(torch.randn(M, K, generator=g), torch.randn(N, K, generator=g), kind)
+    y, dw, db = (torch.full(s, math.nan, device=DEV) for s in ((M, N), (M, N), (M,)))
+    xt, wt = x.t().contiguous().to(DEV), w.t().contiguous().to(DEV)
+    X, W = x.double(), w.double()
+    want, S = X @ W.t(), X.abs() @ W.t().abs()
+    dbw, dbs = X.sum(1), X.abs().sum(1)
+    try:
+        b.debug_set("cfg", cfg)
+        b.debug_set("vec1", vec1)
+        b.linear_fwd(x.to(DEV), w.to(DEV), None, y)  # NT
+        check(y, want, S, K, "y")
+        y.fill_(math.nan)
+        b.linear_bwd(None, wt, x.to(DEV), y, None, None)  # NN: x @ (K x N)
+        check(y, want, S, K, "dx")
+        for splits in (1, 3):  # TN with the column sums of its first operand, whole and in runs
+            b.debug_set("splits", splits)
+            ws = torch.empty(max(1, b.linear_bwd_workspace(wt, None, xt, None, dw, db)), dtype=torch.uint8, device=DEV)
+            b.linear_bwd(wt, None, xt, None, dw, db, workspace=ws)
+            check(dw, want, S, K, f"dw in {splits}")
+            check(db, dbw, dbs, K, f"db in {splits}")
+    finally:
+        b.debug_set("cfg", -1)
+        b.debug_set("vec1", 0)
+        b.debug_set("splits", 0)
+
+
+@pytest.mark.parametrize("kind", ["inf", "tiny_rows"])
+def test_persistent_blocks_recompute_their_tiles(kind):
+    """One block per CU walks several 256x256 tiles: the tiles of a block
+    whose check fails are all written again."""
+    M, N, K = 4352, 4096, 64
+    g = torch.Generator().manual_seed(1)
+    x, w = spoil(torch.randn(M, K, generator=g), torch.randn(N, K, generator=g), kind)
+    bias = torch.randn(N, generator=g)
+    y = torch.full((M, N), math.nan, device=DEV)
+    b.linear_fwd(x.to(DEV), w.to(DEV), bias.to(DEV), y)
+    X, W = x.double(), w.double()
+    check(y, X @ W.t() + bias.double(), X.abs() @ W.t().abs() + bias.double().abs(), K, "y")
+
+
+@pytest.mark.parametrize("kind", ["inf", "tiny_rows_big_other"])
+@pytest.mark.parametrize("stride", [1, 2])
+def test_convolution_of_values_the_split_does_not_serve(kind, stride):
+    """The gathering products, stream-K and the sub-pixel phases included."""
+    n, C, H, CO = 2, 32, 20, 64
+    g = torch.Generator().manual_seed(3)
+    x, w = torch.randn(n, C, H, H, generator=g), torch.randn(CO, C, 3, 3, generator=g) / 17
+    ho = (H + 2 - 3) // stride + 1
+    dy = torch.randn(n, CO, ho, ho, generator=g)
+    if kind == "inf":
+        x[1, 3, 4, 5], dy[0, 7, 2, 2] = math.inf, -math.inf
+    else:
+        x, dy, w = x * 1e-36, dy * 1e-36, w * 1e30
+    cl = torch.channels_last
+    xd, wd, dyd = (t.to(DEV).contiguous(memory_format=cl) for t in (x, w, dy))
+    y, dx, dw, db = torch.empty_like(dyd), torch.empty_like(xd), torch.empty_like(wd), torch.empty(CO, device=DEV)
+    X, W, D = (t.double().requires_grad_() for t in (x, w, dy))
+
+    def grads(a, k, d):
+        a, k = a.detach().requires_grad_(), k.detach().requires_grad_()
+        out = torch.nn.functional.conv2d(a, k, stride=stride, padding=1)
+        ga, gk = torch.autograd.grad(out, (a, k), d)
+        return out.detach(), ga, gk
+
+    try:
+        for sk in (0, 2):
+            b.debug_set("stream_k", sk)
+            b.debug_set("sk_blocks", 5 if sk else 0)
+            b.debug_set("phase_grid", sk)
+            if sk:
+                b.debug_set("cfg", 6)
+            k1 = max(b.conv2d_fwd_workspace(xd, wd, None, y, stride, 1),
+                     b.conv2d_bwd_workspace(xd, wd, dyd, dx, dw, db, stride, 1))
+            ws = torch.empty(max(1, k1), dtype=torch.uint8, device=DEV)
+            b.conv2d_fwd(xd, wd, None, y, stride, 1, workspace=ws)
+            b.conv2d_bwd(xd, wd, dyd, dx, dw, db, stride, 1, workspace=ws)
+            if kind == "inf":
+                # a padded tap is absent here and a zero there: only which results are not finite
+                f, a, c = grads(X, W, D)
+                for got, want in ((y, f), (dx, a), (dw, c)):
+                    assert torch.equal(torch.isfinite(got).cpu(), torch.isfinite(want))
+            else:
+                want = grads(X, W, D)
+                scale = grads(X.abs(), W.abs(), D.abs())
+                for got, v, S, K in zip((y, dx, dw), want, scale, (C * 9, CO * 9, n * ho * ho)):
+                    check(got, v.detach(), S, K, "conv")
+    finally:
+        for k, v in (("stream_k", 1), ("sk_blocks", 0), ("phase_grid", 1), ("cfg", -1)):
+            b.debug_set(k, v)
+
+
+@pytest.mark.parametrize("K,runs", [(64, 1), (4096, 1), (100352, 28)])
+def test_no_further_from_exact_than_fp32_sums(K, runs):
+    """dW = dY^T X of normal values, unsplit or in runs, on the 256x256 tile:
+    the fp32 instructions were 1.4e-7, 1.15e-6 and 1.08e-6 off here."""
+    g = torch.Generator(DEV).manual_seed(K)
+    x, dy = (torch.randn(K, 256, generator=g, device=DEV) for _ in range(2))
+    dw = torch.empty(256, 256, device=DEV)
+    try:
+        b.debug_set("cfg", 6)
+        b.debug_set("splits", runs)
+        ws = torch.empty(max(1, b.linear_bwd_workspace(x, None, dy, None, dw, None)), dtype=torch.uint8, device=DEV)
+        b.linear_bwd(x, None, dy, None, dw, None, workspace=ws)
+    finally:
+        b.debug_set("cfg", -1)
+        b.debug_set("splits", 0)
+    want = dy.double().t() @ x.double()
+    rel = float((dw.double() - want).norm() / want.norm())
+    assert rel <= {64: 1.4e-7, 4096: 1.15e-6, 100352: 1.08e-6}[K], rel
