@@ -21,7 +21,7 @@ SOURCES = ["gemm_f32.hip", "gemm_bf16.hip", "reduce.hip", "elementwise.hip", "co
            "shape.cpp", "capi.cpp", "conv_host.cpp"]
 # what is compiled: (source, extra flags); the fp32 products take most of the
 # time and compile in parts, side by side
-UNITS = ([("gemm_f32.hip", [f"-DMT_F32_PART={n}"]) for n in (3, 4, 1, 2, 5)] +
+UNITS = ([("gemm_f32.hip", [f"-DMT_F32_PART={n}"]) for n in (3, 4, 1, 2, 6, 5)] +
          [(s, []) for s in SOURCES if s != "gemm_f32.hip"])
 COMMON = ["-std=c++17", "-O3", "-fPIC", "-Wall", "-Wno-unused-result",
           f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

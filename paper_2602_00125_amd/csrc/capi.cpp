@@ -217,6 +217,13 @@ int choose_splits(int64_t blocks, int64_t stages, int cfg) {
     int64_t s = std::min<int64_t>(256 / blocks, stages / min_run);
     return s < 1 ? 1 : (int)s;
   }
+  if (mt::gemm_small_cfg(cfg)) {
+    // the block's waves already share the contraction: runs only where a few
+    // tiles would leave most CUs idle for long, each wave of a run keeping 8 K-steps
+    const int64_t waves = cfg == mt::kCfgSmall64 ? 4 : cfg == mt::kCfgSmall32 ? 8 : 16;
+    if (blocks >= 128 || stages < waves * 32) return 1;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(256 / blocks, stages / (waves * 8)));
+  }
   if (blocks >= 512) return 1;
   // the 128x128 DMA tiles with a block on every CU already keep the matrix
   // cores as busy as two blocks per CU do, so a split only adds its finish
@@ -238,7 +245,7 @@ int choose_epi_cfg(int64_t M, int64_t N, bool vec) {
   auto tiles = [&](int64_t bm, int64_t bn) { return cdiv(M, bm) * cdiv(N, bn); };
   if (const int fc = g_force_cfg; fc >= 0) {
     if ((fc == mt::kCfgDma256x256 || fc == mt::kCfgDma128x128) && vec) return fc;
-    if (fc == mt::kCfg64x64) return fc;
+    if (fc == mt::kCfg64x64 || mt::gemm_small_cfg(fc)) return fc;
     return mt::kCfg128x128;
   }
   if (vec && tiles(256, 256) >= 256) return mt::kCfgDma256x256;
@@ -283,7 +290,7 @@ int vec_elems(bool bf16) { return bf16 ? 8 : 4; }
 // 4-byte lanes on 256x256, 256x128, 128x256, the 4-wave 128x128 and the
 // 256x192, 256x96 and 64x384 tiles.
 bool dma_kernel(int cfg, bool vec, bool bf16) {
-  if (cfg < mt::kCfgDma256x256) return false;
+  if (cfg < mt::kCfgDma256x256 || mt::gemm_small_cfg(cfg)) return false;
   if (vec) return true;
   return !bf16 && (cfg == mt::kCfgDma256x256 || cfg == mt::kCfgDma256x128 ||
                    cfg == mt::kCfgDma128x256 || cfg == mt::kCfgDma128x128 ||
@@ -328,14 +335,14 @@ size_t plan_gemm(GemmCall& g, bool may_split) {
     if (!g.bf16 && (dma || g.cfg == mt::kCfg256x128 || g.cfg == mt::kCfg128x256)) {
       if (g.cfg == mt::kCfg256x128) g.cfg = mt::kCfgDma256x128;
       if (g.cfg == mt::kCfg128x256) g.cfg = mt::kCfgDma128x256;
-    } else if (g.cfg != mt::kCfg64x64) {
+    } else if (g.cfg != mt::kCfg64x64 && !mt::gemm_small_cfg(g.cfg)) {
       g.cfg = mt::kCfg128x128;
     }
   }
   // the column sums of A fold into the DMA kernels of plain TN products and
   // of the convolution's weight gradient only
   if (p.colsum && (g.a_kc || (g.conv && g.conv != 2) || p.nred > 0 || p.keep_count != 1 ||
-                   !dma_kernel(g.cfg, g.vec, g.bf16)))
+                   !(dma_kernel(g.cfg, g.vec, g.bf16) || mt::gemm_small_cfg(g.cfg))))
     p.colsum = nullptr;
   p.colsum_part = nullptr;
   const int64_t stages = cdiv(p.K, mt::gemm_tile_k(g.cfg, g.bf16)) * p.red_count;
@@ -383,10 +390,140 @@ size_t plan_gemm(GemmCall& g, bool may_split) {
                   : tiles_bytes;
 }
 
+// ---- small products (gemm_small.hpp) or ring tiles: an estimate of each, in
+// us, fitted to products of 1 to 8192 rows, columns and terms on the box
+// (within about 30%; it only has to rank them).
+
+// A small tile's time: a launch, and per round of 256 blocks (one a CU) what a
+// block costs by itself and per K-step of a wave; `vmax` of the slowest block.
+struct SmallEst {
+  double launch, block;  // launch; one block
+  int64_t tiles;
+};
+SmallEst small_est(const GemmCall& g, int cfg) {
+  const mt::GemmParams& p = g.p;
+  // launch, block, K-step: fp32 64x64 / 32x32 / 16x16 (1024^3 24 us, 512^3 9.4,
+  // 256^3 5.6), bf16 about half (12, 5.6, 4.5)
+  static const double f32[3][3] = {{3.0, 4.5, 3.4}, {2.5, 3.2, 1.9}, {1.5, 2.2, 2.1}};
+  static const double b16[3][3] = {{2.5, 2.5, 1.75}, {2.0, 1.6, 0.95}, {1.5, 1.5, 1.05}};
+  const int i = cfg - mt::kCfgSmall64;
+  const double* c = g.bf16 ? b16[i] : f32[i];
+  const int64_t t = mt::gemm_tile_m(cfg), waves = cfg == mt::kCfgSmall16 ? 16 : 8;
+  const int64_t tiles = cdiv(p.M, t) * cdiv(p.N, t) * p.keep_count * p.splits;
+  // an operand contiguous along k costs more lines per load; a K tail is read
+  // element by element
+  const double step = c[2] * (g.a_kc && g.b_kc ? 1.0 : 0.85) * (g.vec ? 1.0 : 1.15);
+  const int64_t whole = p.K / 32 * p.red_count, tails = p.K % 32 ? p.red_count : 0;
+  const double steps = (double)cdiv(cdiv(whole, p.splits), waves) + 1.5 * (double)cdiv(cdiv(tails, p.splits), waves);
+  return {c[0], c[1] + steps * step, tiles};
+}
+double small_time(const SmallEst& e) { return e.launch + e.block * (double)cdiv(e.tiles, 256); }
+
+// The time of a planned product on the other tiles.
+double ring_time(const GemmCall& g) {
+  const mt::GemmParams& p = g.p;
+  const double blocks = (double)(cdiv(p.M, mt::gemm_tile_m(g.cfg)) * cdiv(p.N, mt::gemm_tile_n(g.cfg)) *
+                                 p.keep_count * p.splits);
+  const double stages = (double)p.stages_per_split;
+  const double rounds = std::ceil(blocks / 256.0);
+  double t;
+  if (g.cfg == mt::kCfg64x64) {
+    // four blocks a CU: 0.5 us (bf16 0.38) a stage until they fill it
+    t = 3.5 + stages * (g.bf16 ? 0.38 : 0.5) * std::max(1.0, blocks / 640.0) * (g.vec ? 1.0 : g.bf16 ? 2.0 : 1.5);
+  } else {
+    // us per stage of one block alone on its CU
+    double per;
+    switch (g.cfg) {
+      case mt::kCfgDma256x256: case mt::kCfgDma256x256w4: per = g.bf16 ? 1.8 : 4.8; break;
+      case mt::kCfgDma256x128: case mt::kCfgDma128x256: case mt::kCfg256x128: case mt::kCfg128x256:
+        per = g.bf16 ? 0.6 : 1.4; break;
+      case mt::kCfgDma128x128k64: per = 2.9; break;
+      case mt::kCfgDma256x96: case mt::kCfgDma64x384: per = 0.85; break;
+      default: per = g.bf16 ? 0.95 : 1.45; break;
+    }
+    if (g.bf16) per *= std::min(1.0, 0.55 + 0.45 * blocks / 256.0);
+    t = 5.0 + rounds * (4.0 + stages * per * (g.vec ? 1.0 : g.bf16 ? 3.0 : 1.3));
+  }
+  if (p.splits > 1) t += 4.0 + (double)(p.splits + 1) * (double)(p.M * p.N * p.keep_count) * 1e-6;
+  return t;
+}
+
+// Whether the operands' rows keep the small kernel's 32-bit offsets.
+bool small_fits(const GemmCall& g) {
+  const int64_t es = g.bf16 ? 2 : 4, lim = (int64_t)1 << 31;
+  return !g.conv && 64 * g.p.lda * es < lim && 64 * g.p.ldb * es < lim && g.p.K < lim / 2 &&
+         cdiv(g.p.K, 32) * g.p.red_count < lim / 2 && g.p.keep_count < lim / 2 && g.p.red_count < lim / 2;
+}
+
+// The small tile that should take a planned product instead, or -1.
+int choose_small(const GemmCall& planned, double* time) {
+  *time = ring_time(planned);
+  int best = -1;
+  if (g_force_cfg >= 0 || !small_fits(planned)) return best;
+  GemmCall g = planned;
+  g.p.splits = 1;
+  for (int cfg : {mt::kCfgSmall64, mt::kCfgSmall32, mt::kCfgSmall16}) {
+    const double t = small_time(small_est(g, cfg));
+    if (t < 0.9 * *time) {
+      *time = t;
+      best = cfg;
+    }
+  }
+  return best;
+}
+
+// The tile on which both gradients of a layer run in one launch, or -1: where
+// that is quicker than one launch after the other (each on its best tile).
+int choose_small_bwd(GemmCall& gdx, GemmCall& gdw, bool may_split) {
+  if (!small_fits(gdx) || !small_fits(gdw)) return -1;
+  int best = -1;
+  if (const int fc = g_force_cfg; fc >= 0) {
+    if (!mt::gemm_small_cfg(fc) || g_force_splits > 0) return -1;
+    best = fc;
+  } else {
+    GemmCall x = gdx, w = gdw;
+    plan_gemm(x, may_split);
+    plan_gemm(w, may_split);
+    const bool db_apart = gdw.p.colsum && !w.p.colsum;
+    double tx, tw;
+    choose_small(x, &tx);
+    const bool w_small = choose_small(w, &tw) >= 0;
+    double least = tx + tw + (db_apart && !w_small ? 5.0 : 0.0);
+    for (int cfg : {mt::kCfgSmall64, mt::kCfgSmall32, mt::kCfgSmall16}) {
+      x.p.splits = w.p.splits = 1;
+      const SmallEst ex = small_est(x, cfg), ew = small_est(w, cfg);
+      const double all = (ex.block * (double)ex.tiles + ew.block * (double)ew.tiles) / 256.0;
+      const double t = ex.launch + std::max(std::max(ex.block, ew.block), all + 0.5 * std::min(ex.block, ew.block));
+      if (t < least) {
+        least = t;
+        best = cfg;
+      }
+    }
+  }
+  if (best < 0) return -1;
+  for (GemmCall* g : {&gdx, &gdw}) {
+    g->cfg = best;
+    plan_gemm(*g, false);
+  }
+  return best;
+}
+
 mt_status launch_gemm(GemmCall& g, hipStream_t stream, void* ws, size_t ws_bytes) {
   mt::GemmParams& p = g.p;
   if (p.M == 0 || p.N == 0 || p.keep_count == 0) return MT_OK;
-  const size_t need = plan_gemm(g, ws != nullptr);
+  const GemmCall asked = g;
+  size_t need = plan_gemm(g, ws != nullptr);
+  if (need > ws_bytes && !g.sk) {  // as it will run: without the split
+    g = asked;
+    need = plan_gemm(g, false);
+  }
+  // (the workspace queries go by the ring tiles' plan, whatever runs)
+  double est;
+  if (const int small = choose_small(g, &est); small >= 0) {
+    g = asked;
+    g.cfg = small;
+    need = plan_gemm(g, ws != nullptr);
+  }
   if (g.sk && need > ws_bytes) g.sk = 0;  // no room for the partial tiles: one tile per block
   if (g.sk) {
     p.partial = (float*)ws;
@@ -583,10 +720,18 @@ mt_status linear_bwd_impl(const mt_tensor* x, const mt_tensor* w, const mt_tenso
   if (ws && ((uintptr_t)ws & 255))
     return fail(MT_ERR_WORKSPACE, "workspace must be 256-byte aligned");
 
+  fold_db = false;
+  if (dx && dw && M > 0 && N > 0 && K > 0) {
+    // both gradients of a small layer (and db) in one launch
+    if (const int cfg = choose_small_bwd(gdx, gdw, ws != nullptr); cfg >= 0) {
+      (void)hipGetLastError();
+      return hip_status(bf ? mt::gemm_small_bwd_bf16(gdx.p, gdw.p, cfg, stream)
+                           : mt::gemm_small_bwd_f32(gdx.p, gdw.p, cfg, stream));
+    }
+  }
   if (dx && M > 0 && K > 0) {
     if ((s = launch_gemm(gdx, stream, ws, ws_bytes))) return s;
   }
-  fold_db = false;
   if (dw && N > 0 && K > 0) {
     if ((s = launch_gemm(gdw, stream, ws, ws_bytes))) return s;
     fold_db = gdw.p.colsum != nullptr;  // the product summed db itself

@@ -3,6 +3,7 @@
 // 16-byte (VEC = 8) or 2-byte (VEC = 1) loads; fp32 bias and output.
 #include "gemm_dma.hpp"
 #include "gemm_kernel.hpp"
+#include "gemm_small.hpp"
 #include "kernels.hpp"
 
 namespace mt {
@@ -96,8 +97,9 @@ static hipError_t launch_epi(const GemmParams& p, bool vec, int cfg, hipStream_t
 
 hipError_t gemm_bf16(const GemmParams& p, bool a_kc, bool b_kc, bool vec, int cfg,
                      hipStream_t stream) {
+  if ((p.act || p.z) && !(a_kc && b_kc)) return hipErrorInvalidValue;
+  if (gemm_small_cfg(cfg)) return gemm_small_bf16(p, a_kc, b_kc, cfg, stream);
   if (p.act || p.z) {
-    if (!a_kc || !b_kc) return hipErrorInvalidValue;
     return launch_epi(p, vec, cfg, stream);
   }
   if (vec) {
@@ -110,6 +112,13 @@ hipError_t gemm_bf16(const GemmParams& p, bool a_kc, bool b_kc, bool vec, int cf
   if (a_kc && !b_kc) return launch_layout<true, false, 1>(p, cfg, stream);
   if (!a_kc && b_kc) return launch_layout<false, true, 1>(p, cfg, stream);
   return launch_layout<false, false, 1>(p, cfg, stream);
+}
+
+hipError_t gemm_small_bf16(const GemmParams& p, bool a_kc, bool b_kc, int cfg, hipStream_t stream) {
+  return gemm::SmallLaunch<__bf16>::run(p, a_kc, b_kc, gemm_tile_m(cfg), stream);
+}
+hipError_t gemm_small_bwd_bf16(const GemmParams& pdx, const GemmParams& pdw, int cfg, hipStream_t stream) {
+  return gemm::SmallLaunch<__bf16>::bwd(pdx, pdw, gemm_tile_m(cfg), stream);
 }
 
 }  // namespace mt

@@ -4,9 +4,10 @@
 //
 // The file compiles whole, or one part at a time for a parallel build
 // (MT_F32_PART: 1 NT, 2 NN, 3 TN and TT, 4 the convolution's products, 5 the
-// dispatch; 0 or unset: all).
+// dispatch, 6 small products; 0 or unset: all).
 #include "gemm_dma.hpp"
 #include "gemm_kernel.hpp"
+#include "gemm_small.hpp"
 #include "kernels.hpp"
 
 #ifndef MT_F32_PART
@@ -283,6 +284,8 @@ hipError_t gemm_f32_conv(const GemmParams& p, int mode, int cfg, hipStream_t str
 #if MT_F32_HAS(5)
 int gemm_tile_m(int cfg) {
   switch (cfg) {
+    case kCfgSmall32: return 32;
+    case kCfgSmall16: return 16;
     case kCfg256x256: case kCfg256x128: case kCfg256x256x64w8: case kCfgDma256x256:
     case kCfgDma256x256w4: case kCfgDma256x128: case kCfgDma256x192: case kCfgDma256x96: return 256;
     case kCfg128x256: case kCfg128x128: case kCfgDma128x256: case kCfgDma128x128:
@@ -292,6 +295,8 @@ int gemm_tile_m(int cfg) {
 }
 int gemm_tile_n(int cfg) {
   switch (cfg) {
+    case kCfgSmall32: return 32;
+    case kCfgSmall16: return 16;
     case kCfg256x256: case kCfg128x256: case kCfg256x256x64w8: case kCfgDma256x256:
     case kCfgDma256x256w4: case kCfgDma128x256: return 256;
     case kCfg256x128: case kCfg128x128: case kCfgDma256x128: case kCfgDma128x128:
@@ -303,6 +308,7 @@ int gemm_tile_n(int cfg) {
   }
 }
 int gemm_tile_k(int cfg, bool bf16) {
+  if (gemm_small_cfg(cfg)) return 32;
   if (cfg == kCfgDma128x128k64) return 64;
   if (cfg == kCfg256x256x64w8) return bf16 ? 64 : 32;
   if (cfg == kCfgDma256x256 || cfg == kCfgDma256x256w4 || cfg == kCfgDma128x128 ||
@@ -314,8 +320,18 @@ int gemm_tile_k(int cfg, bool bf16) {
 hipError_t gemm_f32(const GemmParams& p, bool a_kc, bool b_kc, bool vec, int cfg,
                     hipStream_t stream) {
   if ((p.act || p.z) && !(a_kc && b_kc)) return hipErrorInvalidValue;
+  if (gemm_small_cfg(cfg)) return gemm_small_f32(p, a_kc, b_kc, cfg, stream);
   if (!a_kc) return gemm_f32_tn(p, b_kc, vec, cfg, stream);
   return b_kc ? gemm_f32_nt(p, vec, cfg, stream) : gemm_f32_nn(p, vec, cfg, stream);
+}
+#endif
+
+#if MT_F32_HAS(6)
+hipError_t gemm_small_f32(const GemmParams& p, bool a_kc, bool b_kc, int cfg, hipStream_t stream) {
+  return gemm::SmallLaunch<float>::run(p, a_kc, b_kc, gemm_tile_m(cfg), stream);
+}
+hipError_t gemm_small_bwd_f32(const GemmParams& pdx, const GemmParams& pdw, int cfg, hipStream_t stream) {
+  return gemm::SmallLaunch<float>::bwd(pdx, pdw, gemm_tile_m(cfg), stream);
 }
 #endif
 

@@ -32,7 +32,12 @@ enum GemmCfg {
   kCfgDma256x192 = 13,   // 8 waves, BK = 16, 4-stage ring (112 KB), 1 block per CU
   kCfgDma256x96 = 14,    // 4 waves, BK = 16, 3-stage ring (66 KB), 2 blocks per CU; B K-contiguous
   kCfgDma64x384 = 15,    // 4 waves, BK = 16, 2-stage ring (56 KB), 2 blocks per CU
-  kNumGemmCfg = 16
+  // products too small for those (gemm_small.hpp): one tile a block, its waves
+  // sharing the contraction; any alignment
+  kCfgSmall64 = 16,      // 64x64, 8 waves
+  kCfgSmall32 = 17,      // 32x32, 8 waves
+  kCfgSmall16 = 18,      // 16x16, 16 waves
+  kNumGemmCfg = 19
 };
 int gemm_tile_m(int cfg);
 int gemm_tile_n(int cfg);
@@ -63,6 +68,13 @@ bool gemm_conv_cfg(int cfg);
 // (8 elements) and 16-byte stores; else 2-byte loads and 4-byte stores.
 hipError_t gemm_bf16(const GemmParams& p, bool a_kc, bool b_kc, bool vec, int cfg,
                      hipStream_t stream);
+// The small-product kernel (tiles kCfgSmall*) and its form that computes dX
+// and dW (with its column sums) of one layer in a single launch.
+inline bool gemm_small_cfg(int cfg) { return cfg >= kCfgSmall64 && cfg <= kCfgSmall16; }
+hipError_t gemm_small_f32(const GemmParams& p, bool a_kc, bool b_kc, int cfg, hipStream_t stream);
+hipError_t gemm_small_bf16(const GemmParams& p, bool a_kc, bool b_kc, int cfg, hipStream_t stream);
+hipError_t gemm_small_bwd_f32(const GemmParams& pdx, const GemmParams& pdw, int cfg, hipStream_t stream);
+hipError_t gemm_small_bwd_bf16(const GemmParams& pdx, const GemmParams& pdw, int cfg, hipStream_t stream);
 
 // Split-K finish: C[m][n] (+)= sum_s partial[s][m][n] (+ bias[n]), s ascending.
 // With cs_part (the runs' column sums of A, splits x M floats), also

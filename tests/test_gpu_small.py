@@ -1,0 +1,135 @@
+"""Products too small for the ring tiles: one tile a block, its waves sharing
+the contraction, operands loaded in place (any alignment)."""
+from __future__ import annotations
+
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2602_00125_amd import binding as b  # noqa: E402
+DEV = "cuda:0"
+TILES = {16: 64, 17: 32, 18: 16}
+# every tile edge +-1 and short, whole, one-past and long contractions
+SIZES = [(1, 1, 1), (1, 2, 33), (2, 1, 65), (3, 2, 31), (15, 17, 32), (16, 16, 64), (17, 63, 31), (64, 64, 96),
+         (65, 33, 257), (130, 66, 40), (20, 300, 1000), (257, 31, 545)]
+
+
+def close(got, want, S, K, what, u=2.0 ** -24):
+    """|got - want| <= (2 sqrt(K) + 4) u S: K products, roundings of random sign."""
+    got, err = got.double().cpu(), (got.double().cpu() - want).abs()
+    bound = (2 * math.sqrt(K) + 4) * u * S + 2.0 ** -126
+    assert bool(torch.isfinite(got).all()) and bool((err <= bound).all()), f"{what}: {float((err / bound).max())}"
+
+
+@pytest.mark.parametrize("M,N,K", SIZES)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cfg", [16, 17, 18, -1])
+def test_layer(cfg, dtype, M, N, K):
+    """Y (with bias, and with a nonlinearity), dX, dW and db, one by one and
+    both gradients in one launch, overwriting and accumulating; operands at
+    an odd offset and pitch."""
+    g = torch.Generator().manual_seed(M * 7 + N)
+
+    def view(r, c, odd):
+        t = torch.randn(r, c + odd, generator=g).to(dtype)
+        d = torch.empty(r * (c + odd) + 1, dtype=dtype, device=DEV)[odd:odd + r * (c + odd)].view(r, c + odd)
+        d.copy_(t)
+        return t[:, :c], d[:, :c]
+
+    for odd in (0, 1):
+        (x, xd), (w, wd), (dy, dyd) = view(M, K, odd), view(N, K, odd), view(M, N, odd)
+        bias = torch.randn(N, generator=g)
+        X, W, D = x.double(), w.double(), dy.double()
+        z, h = (torch.full((M, N), math.nan, device=DEV) for _ in range(2))
+        y = torch.full((M, N), math.nan, device=DEV)
+        want = {"dx": (D @ W, D.abs() @ W.abs(), N), "dw": (D.t() @ X, D.t().abs() @ X.abs(), M),
+                "db": (D.sum(0), D.abs().sum(0), M)}
+        try:
+            b.debug_set("cfg", cfg)
+            b.linear_fwd(xd, wd, bias.to(DEV), y)
+            b.linear_act_fwd(xd, wd, bias.to(DEV), "relu", h, z)
+            Z, S = X @ W.t() + bias.double(), X.abs() @ W.t().abs() + bias.double().abs()
+            close(y, Z, S, K, "y")
+            close(z, Z, S, K, "z")
+            assert torch.equal(h, z.clamp(min=0))
+            for names in (("dx", "dw", "db"), ("dx",), ("dw", "db"), ("dx", "dw")):
+                for acc in (False, True):
+                    prior = {n: torch.randn(want[n][0].shape, generator=g) for n in names}
+                    out = {n: (prior[n].to(DEV) if acc else torch.full(want[n][0].shape, math.nan, device=DEV)) for n in names}
+                    b.linear_bwd(xd, wd, dyd, *(out.get(n) for n in ("dx", "dw", "db")), accumulate=acc)
+                    for n in names:
+                        v, s, k = want[n]
+                        if acc:
+                            v, s = v + prior[n].double(), s + prior[n].double().abs()
+                        close(out[n], v, s, k, f"{n} of {names} acc={acc} odd={odd}")
+        finally:
+            b.debug_set("cfg", -1)
+
+
+@pytest.mark.parametrize("cfg", [16, 17, 18])
+@pytest.mark.parametrize("K", [33, 64])
+def test_batched_and_summed(cfg, K):
+    """Broadcast batches and the sums over them, in every operand layout
+    (whole K-steps and a tail in each summed element), and stride-0 views."""
+    g = torch.Generator().manual_seed(cfg)
+    A, B = torch.randn(3, 1, 37, K, generator=g), torch.randn(1, 4, K, 41, generator=g)
+    want, S = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+    one = torch.randn(1, K, generator=g)
+    try:
+        b.debug_set("cfg", cfg)
+        for ta in (False, True):
+            for tb in (False, True):
+                a = (A.mT.contiguous().to(DEV).mT if ta else A.to(DEV))
+                w = (B.mT.contiguous().to(DEV).mT if tb else B.to(DEV))
+                c = torch.full((3, 4, 37, 41), math.nan, device=DEV)
+                b.matmul(a, w, c)
+                close(c, want, S, K, f"c {ta} {tb}")
+                c = torch.full((4, 37, 41), math.nan, device=DEV)
+                b.matmul(a, w, c, reduce_into=True)
+                close(c, want.sum(0), S.sum(0), 3 * K, f"sum {ta} {tb}")
+        # every row of the first operand the same memory
+        c = torch.full((4, 37, 41), math.nan, device=DEV)
+        b.matmul(one.to(DEV).expand(37, K), B[0].to(DEV), c)
+        close(c, one.double().expand(37, K) @ B[0].double(), one.double().abs() @ B[0].double().abs(), K, "expanded")
+    finally:
+        b.debug_set("cfg", -1)
+
+
+@pytest.mark.parametrize("cfg", [16, 17, 18])
+@pytest.mark.parametrize("kind", ["inf", "nan", "huge", "tiny_rows", "tiny_rows_big_other", "zero_rows"])
+def test_values_the_split_does_not_serve(cfg, kind):
+    from test_gpu_split import check, spoil
+    g = torch.Generator().manual_seed(cfg)
+    M, N, K = 210, 70, 136
+    x, w = spoil(torch.randn(M, K, generator=g), torch.randn(N, K, generator=g), kind)
+    y, db = torch.full((M, N), math.nan, device=DEV), torch.full((M,), math.nan, device=DEV)
+    xt, wt = x.t().contiguous().to(DEV), w.t().contiguous().to(DEV)
+    X, W = x.double(), w.double()
+    want, S = X @ W.t(), X.abs() @ W.t().abs()
+    try:
+        b.debug_set("cfg", cfg)
+        b.linear_fwd(x.to(DEV), w.to(DEV), None, y)
+        check(y, want, S, K, "y")
+        b.linear_bwd(None, wt, x.to(DEV), y.fill_(math.nan), None, None)
+        check(y, want, S, K, "dx")
+        b.linear_bwd(wt, None, xt, None, y.fill_(math.nan), db)
+        check(y, want, S, K, "dw")
+        check(db, X.sum(1), X.abs().sum(1), K, "db")
+    finally:
+        b.debug_set("cfg", -1)
+
+
+def test_runs_of_a_long_contraction():
+    """A 16x16 weight gradient over 20000 rows: split over the grid when a
+    workspace is given, whole without one; db in the same launch."""
+    g = torch.Generator().manual_seed(2)
+    x, dy = torch.randn(20000, 16, generator=g), torch.randn(20000, 16, generator=g)
+    X, D = x.double(), dy.double()
+    dw, db = torch.empty(16, 16, device=DEV), torch.empty(16, device=DEV)
+    for ws in (None, torch.empty(1 << 22, dtype=torch.uint8, device=DEV)):
+        b.linear_bwd(x.to(DEV), None, dy.to(DEV), None, dw.fill_(math.nan), db.fill_(math.nan), workspace=ws)
+        close(dw, D.t() @ X, D.t().abs() @ X.abs(), 20000, "dw")
+        close(db, D.sum(0), D.abs().sum(0), 20000, "db")
