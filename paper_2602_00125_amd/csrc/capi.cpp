@@ -952,7 +952,7 @@ mt_status act_bwd_impl(int32_t act, const mt_tensor* z, const mt_tensor* dy, con
       overlaps(db, dz))
     return fail(MT_ERR_ALIAS, "an output overlaps an input or the other output");
   int parts = 1;
-  if (const int fp = g_force_parts; db && M > 0 && N > 0) parts = fp > 0 ? fp : mt::colsum_parts(M, N);
+  if (const int fp = g_force_parts; db && M > 0 && N > 0) parts = fp > 0 ? fp : mt::act_bwd_parts(M, N);
   const size_t need = parts > 1 ? (size_t)parts * N * sizeof(float) : 0;
   if (ws_query) {
     *ws_query = need;

@@ -297,6 +297,17 @@ hipError_t launch_opt(OptBatch b, const Op& op, hipStream_t stream) {
 
 constexpr int kActBwdWaves = 16;
 
+// Row slices of the pullback with db: up to 512 blocks (two a CU), slices of
+// at least two rows a wave (512 x 1024: 2 slices on 8 blocks 13.8 us, 16 on
+// 64 blocks about 5).
+int act_bwd_parts(int64_t M, int64_t N) {
+  const int64_t col_blocks = (N + 255) / 256;
+  int64_t parts = 512 / (col_blocks > 0 ? col_blocks : 1);
+  if (parts > M / (2 * kActBwdWaves)) parts = M / (2 * kActBwdWaves);
+  if (parts > 256) parts = 256;
+  return parts < 1 ? 1 : (int)parts;
+}
+
 hipError_t act_bwd(int act, const float* z, int64_t ldz, const void* dh, int64_t ldh, void* dz,
                    int64_t ldd, bool is_bf16, int64_t M, int64_t N, bool acc_dz, float* db,
                    bool acc_db, float* ws, int parts, hipStream_t stream) {
@@ -331,8 +342,8 @@ hipError_t act_bwd(int act, const float* z, int64_t ldz, const void* dh, int64_t
 }
 
 int mse_parts(int64_t n) {
-  // ~ one block per CU with 64 KB of loads each at least
-  int64_t parts = (n + 16383) / 16384;
+  // blocks of at least four 16-byte loads a lane from each operand
+  int64_t parts = (n + 4095) / 4096;
   if (parts > 1024) parts = 1024;
   if (parts < 1) parts = 1;
   return (int)parts;

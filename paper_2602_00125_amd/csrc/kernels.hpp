@@ -119,6 +119,7 @@ hipError_t parts_finish(const float* ws, int parts, int64_t N, float* out, bool 
 hipError_t act_bwd(int act, const float* z, int64_t ldz, const void* dh, int64_t ldh, void* dz,
                    int64_t ldd, bool is_bf16, int64_t M, int64_t N, bool acc_dz, float* db,
                    bool acc_db, float* ws, int parts, hipStream_t stream);
+int act_bwd_parts(int64_t M, int64_t N);
 
 // Mean squared error over n contiguous fp32 elements: *loss = sum (p - t)^2 / n
 // (nullable), dp = 2 (p - t) / n (nullable). ws: room for `parts` floats

@@ -11,12 +11,11 @@
 //   are added by a second pass in slice order: no atomics, bit-identical
 //   reruns.
 // * reduce_strided: the same add pullback for any broadcast (the gradient of
-//   an operand that was expanded along some axes). When the innermost axis
-//   of the gradient is kept, a thread per output walks the summed axes
-//   (coalesced along the kept axis). When the innermost axis is summed, a
-//   wave per output strides over it and the 64 lane sums are combined with
-//   DPP row operations (quad_perm, row_half_mirror, row_mirror) and a final
-//   fixed-order sum of the four row results.
+//   an operand that was expanded along some axes). Bound by HBM, so every
+//   form keeps the lanes' loads consecutive (16 bytes each where the strides
+//   allow), four of them in flight, and cuts long sums into parts that fill
+//   the chip (a second pass adds the parts in order). Whether the innermost
+//   axis of the gradient is kept or summed decides what runs along the lanes.
 // * splitk_finish: fixed-order sum of split-K partial tiles.
 #include <hip/hip_runtime.h>
 
@@ -222,63 +221,137 @@ __global__ __launch_bounds__(256) void fill_kernel(float* out, int64_t n, float 
   if (i < n) out[i] = v;
 }
 
-__device__ __forceinline__ int64_t decode(int64_t flat, int nd, const int64_t* shape,
-                                          const int64_t* stride) {
+// Element offset of a flat index over nd dims. I: 32 bits where the count
+// fits (a fraction of the instructions of 64-bit division).
+template <typename I>
+__device__ __forceinline__ int64_t decode(I flat, int nd, const int64_t* shape, const int64_t* stride) {
   int64_t off = 0;
-  for (int d = nd - 1; d >= 0; --d) {
-    const int64_t i = flat % shape[d];
-    flat /= shape[d];
-    off += i * stride[d];
+  for (int d = nd - 1; d > 0; --d) {
+    const I n = (I)shape[d], q = flat / n;
+    off += (int64_t)(flat - q * n) * stride[d];
+    flat = q;
   }
-  return off;
+  return nd > 0 ? off + (int64_t)flat * stride[0] : off;
 }
 
-// Thread per output element; summed index range [r0, r1) of part blockIdx.y.
-__global__ __launch_bounds__(256) void reduce_outer_kernel(const float* x, const ReducePlan plan,
-                                                           float* out, int accumulate, float* ws,
-                                                           int64_t red_per_part) {
-  const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (o >= plan.keep_count) return;
-  const int64_t base = decode(o, plan.nkeep, plan.keep_shape, plan.keep_stride);
-  const int64_t r0 = (int64_t)blockIdx.y * red_per_part;
-  const int64_t r1 = (r0 + red_per_part) < plan.red_count ? (r0 + red_per_part) : plan.red_count;
-  float s = 0.f;
-  for (int64_t r = r0; r < r1; ++r) s += x[base + decode(r, plan.nred, plan.red_shape, plan.red_stride)];
-  if (gridDim.y > 1) ws[(int64_t)blockIdx.y * plan.keep_count + o] = s;
-  else out[o] = accumulate ? out[o] + s : s;
-}
+template <int VEC>
+struct Lane;
+template <>
+struct Lane<1> {
+  using V = float;
+  static __device__ __forceinline__ float sum(V v) { return v; }
+};
+template <>
+struct Lane<4> {
+  using V = f32x4;
+  static __device__ __forceinline__ float sum(V v) { return (v[0] + v[1]) + (v[2] + v[3]); }
+};
 
-// DPP butterfly inside each row of 16 lanes, then the 4 row sums in order.
-__device__ __forceinline__ float wave_sum(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false)); // row_half_mirror
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false)); // row_mirror
-  const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-  const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-  const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-  const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-  return ((r0 + r1) + r2) + r3;
-}
-
-// Wave per output element: the innermost summed axis (stride red_stride[last])
-// is spread over the lanes; outer summed axes are walked in order.
-__global__ __launch_bounds__(256) void reduce_inner_kernel(const float* x, const ReducePlan plan,
-                                                           float* out, int accumulate) {
-  const int lane = threadIdx.x & 63;
-  const int64_t o = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o >= plan.keep_count) return;  // wave-uniform
-  const int64_t base = decode(o, plan.nkeep, plan.keep_shape, plan.keep_stride);
-  const int last = plan.nred - 1;
-  const int64_t inner = plan.red_shape[last], istride = plan.red_stride[last];
-  const int64_t outer = plan.red_count / inner;
-  float s = 0.f;
-  for (int64_t r = 0; r < outer; ++r) {
-    const int64_t ob = base + decode(r, last, plan.red_shape, plan.red_stride);
-    for (int64_t i = lane; i < inner; i += 64) s += x[ob + i * istride];
+// The innermost axis of the gradient is kept: a thread per VEC consecutive
+// outputs, LX threads of the block along the outputs and 256 / LX of them
+// interleaved over the summed index, so that short rows fill the lanes too;
+// their sums meet in LDS. Summed range [y * per, (y + 1) * per) of part y.
+template <typename I, int VEC>
+__global__ __launch_bounds__(256) void reduce_outer_kernel(const float* x, const ReducePlan plan, float* out,
+                                                           int accumulate, float* ws, int64_t per, int lx_shift) {
+  using V = typename Lane<VEC>::V;
+  __shared__ V red[256];
+  const int tid = threadIdx.x, lx = 1 << lx_shift, ly = 256 >> lx_shift;
+  const int tx = tid & (lx - 1), ty = tid >> lx_shift;
+  const int64_t o = ((int64_t)blockIdx.x * lx + tx) * VEC;
+  V s = {};
+  if (o < plan.keep_count) {
+    const float* p = x + decode<I>((I)o, plan.nkeep, plan.keep_shape, plan.keep_stride);
+    const int64_t r0 = (int64_t)blockIdx.y * per;
+    const int64_t r1 = r0 + per < plan.red_count ? r0 + per : plan.red_count;
+    constexpr int U = 4;  // loads in flight
+    int64_t r = r0 + ty;
+    if (plan.nred == 1) {
+      const int64_t st = plan.red_stride[0];
+      for (; r + (U - 1) * ly < r1; r += U * ly) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = *(const V*)(p + (r + u * ly) * st);
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
+      }
+      for (; r < r1; r += ly) s += *(const V*)(p + r * st);
+    } else {
+      for (; r + (U - 1) * ly < r1; r += U * ly) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          v[u] = *(const V*)(p + decode<I>((I)(r + u * ly), plan.nred, plan.red_shape, plan.red_stride));
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
+      }
+      for (; r < r1; r += ly) s += *(const V*)(p + decode<I>((I)r, plan.nred, plan.red_shape, plan.red_stride));
+    }
   }
-  s = wave_sum(s);
-  if (lane == 0) out[o] = accumulate ? out[o] + s : s;
+  red[tid] = s;
+  for (int h = ly / 2; h > 0; h >>= 1) {
+    __syncthreads();
+    if (ty < h) red[tid] += red[tid + (h << lx_shift)];
+  }
+  if (ty != 0 || o >= plan.keep_count) return;
+  s = red[tid];
+  float* dst = gridDim.y > 1 ? ws + (int64_t)blockIdx.y * plan.keep_count + o : out + o;
+  const bool add = gridDim.y == 1 && accumulate;
+  const float* e = (const float*)&s;
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) dst[i] = add ? dst[i] + e[i] : e[i];
+}
+
+// The innermost axis of the gradient is summed: G lanes per output (a group
+// of a wave, or the block's four waves, 256) stride over the flat summed
+// index VEC elements at a time, so that the lanes' loads are consecutive;
+// their sums meet by lane exchanges, and the four waves' in LDS.
+template <typename I, int VEC, int G>
+__global__ __launch_bounds__(256) void reduce_inner_kernel(const float* x, const ReducePlan plan, float* out,
+                                                           int accumulate, float* ws, int64_t per) {
+  using V = typename Lane<VEC>::V;
+  const int tid = threadIdx.x, lane = tid & (G - 1);
+  const int64_t o = (int64_t)blockIdx.x * (256 / G) + tid / G;
+  V s = {};
+  if (o < plan.keep_count) {
+    const float* p = x + decode<I>((I)o, plan.nkeep, plan.keep_shape, plan.keep_stride);
+    const int64_t r0 = (int64_t)blockIdx.y * per;
+    const int64_t r1 = r0 + per < plan.red_count ? r0 + per : plan.red_count;
+    constexpr int U = 4;  // loads in flight
+    int64_t r = r0 + lane * VEC;
+    if (plan.nred == 1) {  // (stride 1)
+      for (; r + (U - 1) * G * VEC < r1; r += U * G * VEC) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = *(const V*)(p + r + u * G * VEC);
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
+      }
+      for (; r < r1; r += G * VEC) s += *(const V*)(p + r);
+    } else {
+      for (; r + (U - 1) * G * VEC < r1; r += U * G * VEC) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          v[u] = *(const V*)(p + decode<I>((I)(r + u * G * VEC), plan.nred, plan.red_shape, plan.red_stride));
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
+      }
+      for (; r < r1; r += G * VEC) s += *(const V*)(p + decode<I>((I)r, plan.nred, plan.red_shape, plan.red_stride));
+    }
+  }
+  float t = Lane<VEC>::sum(s);
+#pragma unroll
+  for (int h = (G < 64 ? G : 64) / 2; h > 0; h >>= 1) t += __shfl_xor(t, h);
+  if constexpr (G == 256) {
+    __shared__ float red[4];
+    if ((tid & 63) == 0) red[tid >> 6] = t;
+    __syncthreads();
+    t = (red[0] + red[1]) + (red[2] + red[3]);
+  }
+  if (lane != 0 || o >= plan.keep_count) return;
+  if (gridDim.y > 1) ws[(int64_t)blockIdx.y * plan.keep_count + o] = t;
+  else out[o] = accumulate ? out[o] + t : t;
 }
 
 }  // namespace
@@ -329,36 +402,85 @@ hipError_t colsum(const void* x, bool is_bf16, int64_t M, int64_t N, int64_t ld,
   return hipGetLastError();
 }
 
+// The innermost axis of the gradient is summed (contiguously).
+static bool reduce_is_inner(const ReducePlan& plan) {
+  return plan.nred > 0 && plan.red_stride[plan.nred - 1] == 1 &&
+         (plan.nkeep == 0 || plan.keep_stride[plan.nkeep - 1] != 1);
+}
+
+// Parts of the summed range: about 1024 blocks of 256 lanes where the outputs
+// alone give fewer, each part at least 16 elements a lane (32 x 128 x 4096
+// summed to 128 values: one wave an output 526 us, 8 parts of a block each
+// about 20 us).
 int reduce_parts(const ReducePlan& plan) {
   if (plan.nred == 0 || plan.keep_count == 0) return 1;
-  // split long sums when there are too few outputs to fill the chip
-  const int64_t blocks = (plan.keep_count + 255) / 256;
-  if (blocks >= 1024 || plan.red_count < 256) return 1;
+  const int64_t elems = plan.keep_count * plan.red_count;
+  // lanes-worth of outputs per block, as the launch below takes them
+  const int64_t blocks = reduce_is_inner(plan) ? plan.keep_count : (plan.keep_count + 255) / 256;
+  if (plan.red_count < 256 || blocks >= 1024) return 1;
   int64_t parts = 1024 / blocks;
+  parts = parts < elems / (blocks * 4096) ? parts : elems / (blocks * 4096);
   if (parts > plan.red_count / 64) parts = plan.red_count / 64;
-  if (parts < 1) parts = 1;
-  return (int)parts;
+  return parts < 1 ? 1 : (int)parts;
+}
+
+template <typename I>
+static hipError_t reduce_launch(const float* x, const ReducePlan& plan, float* out, bool accumulate, float* ws,
+                                int parts, hipStream_t stream) {
+  // 16-byte loads: every row of the innermost axis and every stride a whole
+  // number of them
+  auto fours = [](int n, const int64_t* st) {
+    for (int i = 0; i < n; ++i)
+      if (st[i] % 4 != 0) return false;
+    return true;
+  };
+  const int64_t per4 = (((plan.red_count + parts - 1) / parts) + 3) / 4 * 4;
+  if (reduce_is_inner(plan)) {
+    const int last = plan.nred - 1;
+    const bool vec = (uintptr_t)x % 16 == 0 && plan.red_shape[last] % 4 == 0 && fours(plan.nkeep, plan.keep_stride) &&
+                     fours(last, plan.red_stride);
+    const int64_t lanes = vec ? per4 / 4 : per4;  // lanes that one pass over a part's range fills
+#define MT_REDUCE(VV, GG)                                                                                        \
+  hipLaunchKernelGGL((reduce_inner_kernel<I, VV, GG>),                                                           \
+                     dim3((unsigned)((plan.keep_count + 256 / GG - 1) / (256 / GG)), (unsigned)parts), dim3(256), 0, \
+                     stream, x, plan, out, (int)accumulate, ws, per4)
+    // a group for each output; the block's 256 lanes once an output has four
+    // loads for each of them
+    if (lanes >= 1024) { if (vec) MT_REDUCE(4, 256); else MT_REDUCE(1, 256); }
+    else if (lanes > 32) { if (vec) MT_REDUCE(4, 64); else MT_REDUCE(1, 64); }
+    else if (lanes > 8) { if (vec) MT_REDUCE(4, 16); else MT_REDUCE(1, 16); }
+    else { if (vec) MT_REDUCE(4, 4); else MT_REDUCE(1, 4); }
+#undef MT_REDUCE
+  } else {
+    const bool vec = (uintptr_t)x % 16 == 0 && plan.nkeep > 0 && plan.keep_stride[plan.nkeep - 1] == 1 &&
+                     plan.keep_shape[plan.nkeep - 1] % 4 == 0 && fours(plan.nkeep - 1, plan.keep_stride) &&
+                     fours(plan.nred, plan.red_stride);
+    const int64_t groups = vec ? plan.keep_count / 4 : plan.keep_count;
+    const int64_t per = plan.red_count > 0 ? (plan.red_count + parts - 1) / parts : 0;
+    // threads along the outputs: all 256 where the outputs alone fill the
+    // chip, else 64 or fewer, the rest of the block over the summed index
+    int sh = groups >= 256 * 512 || per < 4 ? 8 : 6;
+    while (sh > 0 && ((int64_t)1 << (sh - 1)) >= groups) --sh;
+    const dim3 grid((unsigned)((groups + (1 << sh) - 1) >> sh), (unsigned)parts);
+    if (vec)
+      hipLaunchKernelGGL((reduce_outer_kernel<I, 4>), grid, dim3(256), 0, stream, x, plan, out, (int)accumulate, ws,
+                         per, sh);
+    else
+      hipLaunchKernelGGL((reduce_outer_kernel<I, 1>), grid, dim3(256), 0, stream, x, plan, out, (int)accumulate, ws,
+                         per, sh);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || parts == 1) return e;
+  return parts_finish(ws, parts, plan.keep_count, out, accumulate, stream);
 }
 
 hipError_t reduce_strided(const float* x, const ReducePlan& plan, float* out, bool accumulate,
                           float* ws, int parts, hipStream_t stream) {
   if (plan.keep_count <= 0) return hipSuccess;
-  const bool inner = plan.nred > 0 && plan.red_stride[plan.nred - 1] == 1 &&
-                     (plan.nkeep == 0 || plan.keep_stride[plan.nkeep - 1] != 1);
-  if (inner) {
-    hipLaunchKernelGGL(reduce_inner_kernel, dim3((unsigned)((plan.keep_count + 3) / 4)), dim3(256),
-                       0, stream, x, plan, out, (int)accumulate);
-    return hipGetLastError();
-  }
-  if (!ws) parts = 1;
-  const int64_t per = plan.red_count > 0 ? (plan.red_count + parts - 1) / parts : 0;
-  hipLaunchKernelGGL(reduce_outer_kernel, dim3((unsigned)((plan.keep_count + 255) / 256), parts),
-                     dim3(256), 0, stream, x, plan, out, (int)accumulate, ws, per);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || parts == 1) return e;
-  hipLaunchKernelGGL(parts_finish_kernel, dim3((unsigned)((plan.keep_count + 255) / 256)),
-                     dim3(256), 0, stream, ws, parts, plan.keep_count, out, (int)accumulate);
-  return hipGetLastError();
+  if (!ws || parts < 1) parts = 1;
+  if (plan.keep_count < (int64_t)1 << 31 && plan.red_count < (int64_t)1 << 31)
+    return reduce_launch<uint32_t>(x, plan, out, accumulate, ws, parts, stream);
+  return reduce_launch<uint64_t>(x, plan, out, accumulate, ws, parts, stream);
 }
 
 hipError_t splitk_finish(const float* partial, int splits, int64_t M, int64_t N, float* c,

@@ -133,3 +133,44 @@ def test_runs_of_a_long_contraction():
         b.linear_bwd(x.to(DEV), None, dy.to(DEV), None, dw.fill_(math.nan), db.fill_(math.nan), workspace=ws)
         close(dw, D.t() @ X, D.t().abs() @ X.abs(), 20000, "dw")
         close(db, D.sum(0), D.abs().sum(0), 20000, "db")
+
+
+# outputs and sums around every group size (4, 16, 64 and 256 lanes), with
+# and without 16-byte rows, one and several summed axes, views
+REDUCTIONS = [((3, 5, 7), k) for k in ("a", "b", "c", "ab", "ac", "bc", "")] + \
+             [((4, 3, 8), k) for k in ("a", "b", "c", "ab", "ac", "bc", "")] + \
+             [((2, 130, 36), k) for k in ("a", "b", "c", "ab", "ac", "bc")] + \
+             [((33, 2, 1028), k) for k in ("a", "b", "ab", "ac")] + [((1, 1, 20000), ""), ((700, 3, 40), "b"),
+              ((5, 1, 4101), "a"), ((4096, 2, 4), "c"), ((2, 600, 260), "ac")]
+
+
+@pytest.mark.parametrize("shape,keep", REDUCTIONS)
+@pytest.mark.parametrize("view", ["whole", "pitch", "permuted", "expanded"])
+def test_reduction(shape, keep, view):
+    g = torch.Generator().manual_seed(sum(shape))
+    t = torch.randn(shape, generator=g)
+    x = t.to(DEV)
+    if view == "pitch":
+        x = torch.nn.functional.pad(x, (1, 2))[..., 1:-2]
+    elif view == "permuted":
+        x = x.permute(2, 0, 1).contiguous().permute(1, 2, 0)
+    elif view == "expanded":
+        t = t[:, :1].expand(shape)
+        x = x[:, :1].expand(shape)
+    axes = [i for i, a in enumerate("abc") if a not in keep]
+    want = t.double().sum(axes, keepdim=True) if axes else t.double()
+    S = t.double().abs().sum(axes, keepdim=True) if axes else t.double().abs()
+    n = t.numel() // want.numel()
+    for parts, acc in ((0, False), (0, True), (3, False)):
+        b.debug_set("parts", parts)
+        try:
+            prior = torch.randn(want.shape, generator=g)
+            out = prior.to(DEV) if acc else torch.full(want.shape, math.nan, device=DEV)
+            k = b.reduce_broadcast_grad_workspace(x, out)
+            for ws in (None, torch.empty(k, dtype=torch.uint8, device=DEV) if k else None):
+                got = out.clone()
+                b.reduce_broadcast_grad(x, got, accumulate=acc, workspace=ws)
+                p = prior.double() if acc else torch.zeros_like(want)
+                close(got, want + p, S + p.abs(), n, f"{parts} {acc} {ws is None}")
+        finally:
+            b.debug_set("parts", 0)
