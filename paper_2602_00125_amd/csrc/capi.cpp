@@ -206,8 +206,8 @@ int choose_cfg_aligned(int64_t M, int64_t N, int64_t batch, int64_t stages, bool
 
 // Split-K runs for a grid of `blocks` tiles over `stages` K-stages: below
 // two blocks per CU, aim for ~512 blocks in all, with at least 8 stages per
-// run and at most 16 runs.
-int choose_splits(int64_t blocks, int64_t stages, int cfg) {
+// run and at most `most` runs.
+int choose_splits(int64_t blocks, int64_t stages, int cfg, int64_t most) {
   if (const int fs = g_force_splits; fs > 0) return (int)std::min<int64_t>(fs, std::max<int64_t>(stages, 1));
   if (cfg == mt::kCfgDma256x256 || cfg == mt::kCfgDma128x128k64 || cfg == mt::kCfgDma256x192) {
     // one block per CU: runs that together fill the 256 CUs once, each at
@@ -233,7 +233,7 @@ int choose_splits(int64_t blocks, int64_t stages, int cfg) {
   // two blocks per CU: at most 512 blocks, so that the grid stays one wave
   int64_t s = 512 / blocks;
   s = std::min<int64_t>(s, stages / 8);
-  s = std::min<int64_t>(s, 16);
+  s = std::min<int64_t>(s, most);
   return s < 1 ? 1 : (int)s;
 }
 
@@ -376,7 +376,10 @@ size_t plan_gemm(GemmCall& g, bool may_split) {
   }
   const int64_t blocks = cdiv(p.M, mt::gemm_tile_m(g.cfg)) * cdiv(p.N, mt::gemm_tile_n(g.cfg)) *
                          p.keep_count;
-  const int want = choose_splits(blocks, stages, g.cfg);
+  // a convolution's weight gradient is few tiles over every output pixel
+  // (16 x 64 x 28 x 28 outputs, 128 3x3 filters: 5 tiles over 12544, 16 runs on
+  // 80 blocks 57 us): as many runs of 8 stages as fill the chip
+  const int want = choose_splits(blocks, stages, g.cfg, g.conv == 2 ? 128 : 16);
   if (want <= 1) return 0;
   const int64_t per = cdiv(stages, want);
   const int64_t splits = cdiv(stages, per);

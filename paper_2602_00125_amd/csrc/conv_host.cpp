@@ -454,14 +454,16 @@ mt_status conv_bwd_impl(const mt_tensor* x, const mt_tensor* w, const mt_tensor*
                      [](const DgradPhase& l, const DgradPhase& r) { return l.K > r.K; });
     int64_t rows = 0;
     for (const DgradPhase& ph : phases) rows += ph.M;
-    // one grid of 256x256 tiles where that tile fits the channels (measured at
-    // 32 x 256 x 56 x 56, 3x3, stride 2: dx 0.308 ms against 0.355 for a launch
-    // per phase; with 128 channels half of every tile would idle: 0.28 against 0.20)
+    // one grid for every phase, so that the short phases fill the CUs the long
+    // one leaves idle: 256x256 tiles where they fit the channels (32 x 256 x 56
+    // x 56, 3x3, stride 2: dx 0.308 ms against 0.355 for a launch per phase;
+    // with 128 channels half of every tile would idle: 0.28 against 0.20),
+    // else 128x128 (16 x 64 x 56 x 56 to 128 channels: four launches of 22 us
+    // with 98 tiles each, one of 392)
     const double used = (double)g.C / (double)(cdiv(g.C, 256) * 256);
     const int pg = g_phase_grid;
-    const bool one_grid = pg == 2 || (pg == 1 && rows >= 256 * 64 && used >= 0.9);
-    if (one_grid && !phases.empty() && (int)phases.size() <= mt::kMaxConvPhases && g.C % 4 == 0) {
-      // one grid of 256x256 tiles: every phase's tiles run side by side
+    const int tile = pg == 2 || (rows >= 256 * 64 && used >= 0.9) ? 256 : 128;
+    if (pg != 0 && !phases.empty() && (int)phases.size() <= mt::kMaxConvPhases && g.C % 4 == 0) {
       mt::ConvPhases tab;
       std::memset(&tab, 0, sizeof(tab));
       tab.n = (int32_t)phases.size();
@@ -470,12 +472,12 @@ mt_status conv_bwd_impl(const mt_tensor* x, const mt_tensor* w, const mt_tensor*
         mt::ConvPhase& f = tab.ph[k];
         f.M = ph.M;
         f.K = ph.K;
-        f.tiles_m = (int32_t)cdiv(ph.M, 256);
+        f.tiles_m = (int32_t)cdiv(ph.M, tile);
         f.u0 = ph.cg.u0; f.v0 = ph.cg.v0; f.ph = ph.cg.ph; f.pw = ph.cg.pw;
         f.rows = ph.cg.HO; f.cols = ph.cg.WO; f.kw = ph.cg.KW; f.h0 = ph.cg.h0; f.w0 = ph.cg.w0;
         f.wo_mag = ph.cg.wo_mag; f.ho_mag = ph.cg.ho_mag;
         f.wo_shift = ph.cg.wo_shift; f.ho_shift = ph.cg.ho_shift;
-        tab.tile0[k + 1] = tab.tile0[k] + f.tiles_m * (int32_t)cdiv(g.C, 256);
+        tab.tile0[k + 1] = tab.tile0[k] + f.tiles_m * (int32_t)cdiv(g.C, tile);
       }
       mt::GemmParams p;
       init_params(&p);
@@ -490,7 +492,7 @@ mt_status conv_bwd_impl(const mt_tensor* x, const mt_tensor* w, const mt_tensor*
       p.ldc = g.C;
       p.accumulate = acc;
       (void)hipGetLastError();
-      if ((s = hip_status(mt::gemm_f32_conv_phases(p, tab, stream)))) return s;
+      if ((s = hip_status(mt::gemm_f32_conv_phases(p, tab, tile, stream)))) return s;
     } else {
       for (const DgradPhase& ph : phases) {
         GemmCall gp{};

@@ -174,3 +174,18 @@ def test_reduction(shape, keep, view):
                 close(got, want + p, S + p.abs(), n, f"{parts} {acc} {ws is None}")
         finally:
             b.debug_set("parts", 0)
+
+
+from test_gpu_conv import PHASE_CASES, check as conv_check, make as conv_make, run as conv_run  # noqa: E402
+
+
+@pytest.mark.parametrize("case", PHASE_CASES, ids=[f"p{i}" for i in range(len(PHASE_CASES))])
+def test_strided_input_gradient_in_one_grid_of_small_tiles(case):
+    """Every sub-pixel phase in one grid of 128x128 tiles (the default for
+    gradients that do not fill 256x256 ones), against the oracle."""
+    x, w, bias, dy = conv_make(case, seed=73)
+    conv_check(case, x, w, bias, dy, *conv_run(case, x, w, bias, dy))
+    N, C, H, W, CO, KH, KW = case[:7]
+    prior = (torch.randn(N, C, H, W, device=DEV), None, None)
+    got = conv_run(case, x, w, bias, dy, outputs=("dx",), accumulate=True, prior=prior)
+    conv_check(case, x, w, bias, dy, got[0], got[1], None, None, prior=prior)
