@@ -3,8 +3,11 @@
 Every function here builds ``mt_tensor`` descriptors from torch tensors
 (device memory owned by torch) and calls the C entry point of the same name
 on the current HIP stream; all arithmetic runs in the library's HIP kernels.
-Importing this module raises ImportError when the library has not been built
-(``python paper_2602_00125_amd/build.py``): there is no fallback path.
+The entry points of a training loop take their descriptors from a native
+module (``csrc/pymarshal.cpp``), the queries and helpers from ctypes.
+Importing this module raises ImportError when the library or that module has
+not been built (``python paper_2602_00125_amd/build.py``): there is no
+fallback path.
 """
 from __future__ import annotations
 
@@ -12,6 +15,11 @@ import ctypes
 import os
 
 import torch
+
+try:
+    from . import _marshal as _m
+except ImportError as e:
+    raise ImportError("the marshalling module is not built; run `python paper_2602_00125_amd/build.py`") from e
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # MT_LIB_OVERRIDE: a differently built copy of the library (the host-only
@@ -142,18 +150,19 @@ def _stream(stream) -> int:
     return int(stream)
 
 
-def _ws(workspace):
-    if workspace is None:
-        return None, 0
-    assert workspace.is_cuda
-    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
+_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
+def _current_stream() -> int:
+    return _raw_stream(_device())
+
+
+_m.init(lib._handle, torch.float32, torch.bfloat16, desc, _current_stream, _stream)
 
 
 def linear_fwd(x, w, b, y, stream=None) -> None:
     """y = x w^T + b on the device (b may be None)."""
-    dx_, dw_, db_, dy_ = desc(x), desc(w), desc(b), desc(y)
-    _check(lib.mt_linear_fwd(_ref(dx_), _ref(dw_), _ref(db_), _ref(dy_), _stream(stream)),
-           "mt_linear_fwd")
+    _check(_m.linear_fwd(x, w, b, y, stream), "mt_linear_fwd")
 
 
 def linear_bwd_workspace(x, w, dy, dx=None, dw=None, db=None) -> int:
@@ -167,10 +176,8 @@ def linear_bwd_workspace(x, w, dy, dx=None, dw=None, db=None) -> int:
 def linear_bwd(x, w, dy, dx=None, dw=None, db=None, accumulate=False, workspace=None,
                stream=None) -> None:
     """dx = dy w, dw = dy^T x, db = column sums of dy (None skips an output)."""
-    ds = [desc(t) for t in (x, w, dy, dx, dw, db)]
-    ptr, nbytes = _ws(workspace)
-    _check(lib.mt_linear_bwd(*[_ref(d) for d in ds], ACCUMULATE if accumulate else 0, ptr, nbytes,
-                             _stream(stream)), "mt_linear_bwd")
+    _check(_m.linear_bwd(x, w, dy, dx, dw, db, ACCUMULATE if accumulate else 0, workspace, stream),
+           "mt_linear_bwd")
 
 
 def linear_bwd_noalloc(x, w, dy, dx=None, dw=None, db=None, accumulate=False,
@@ -192,10 +199,7 @@ def matmul_workspace(a, b, c, accumulate=False, reduce_into=False) -> int:
 def matmul(a, b, c, accumulate=False, reduce_into=False, workspace=None, stream=None) -> None:
     """c = a @ b with broadcasting (c summed over broadcast axes with reduce_into)."""
     flags = (ACCUMULATE if accumulate else 0) | (REDUCE_INTO if reduce_into else 0)
-    da, db_, dc = desc(a), desc(b), desc(c)
-    ptr, nbytes = _ws(workspace)
-    _check(lib.mt_matmul(_ref(da), _ref(db_), _ref(dc), flags, ptr, nbytes, _stream(stream)),
-           "mt_matmul")
+    _check(_m.matmul(a, b, c, flags, workspace, stream), "mt_matmul")
 
 
 def workspace_bytes(op: str, *tensors) -> int:
@@ -219,10 +223,8 @@ def reduce_broadcast_grad_workspace(grad_out, grad_in) -> int:
 
 def reduce_broadcast_grad(grad_out, grad_in, accumulate=False, workspace=None, stream=None) -> None:
     """grad_in = grad_out summed over the axes grad_in was broadcast along."""
-    ptr, nbytes = _ws(workspace)
-    _check(lib.mt_reduce_broadcast_grad(_ref(desc(grad_out)), _ref(desc(grad_in)),
-                                        ACCUMULATE if accumulate else 0, ptr, nbytes,
-                                        _stream(stream)), "mt_reduce_broadcast_grad")
+    _check(_m.reduce_broadcast_grad(grad_out, grad_in, ACCUMULATE if accumulate else 0, workspace, stream),
+           "mt_reduce_broadcast_grad")
 
 
 def _act_code(act) -> int:
@@ -231,9 +233,7 @@ def _act_code(act) -> int:
 
 def linear_act_fwd(x, w, b, act, y, z=None, stream=None) -> None:
     """y = act(x w^T + b); z (optional) receives the pre-activation."""
-    ds = [desc(t) for t in (x, w, b)]
-    _check(lib.mt_linear_act_fwd(*[_ref(d) for d in ds], _act_code(act), _ref(desc(z)),
-                                 _ref(desc(y)), _stream(stream)), "mt_linear_act_fwd")
+    _check(_m.linear_act_fwd(x, w, b, _act_code(act), z, y, stream), "mt_linear_act_fwd")
 
 
 def act_bwd_workspace(act, z, dy, dz, db=None) -> int:
@@ -246,10 +246,8 @@ def act_bwd_workspace(act, z, dy, dz, db=None) -> int:
 
 def act_bwd(act, z, dy, dz, db=None, accumulate=False, workspace=None, stream=None) -> None:
     """dz = dy * act'(z); db = column sums of dz (None skips it)."""
-    ds = [desc(t) for t in (z, dy, dz, db)]
-    ptr, nbytes = _ws(workspace)
-    _check(lib.mt_act_bwd(_act_code(act), *[_ref(d) for d in ds], ACCUMULATE if accumulate else 0,
-                          ptr, nbytes, _stream(stream)), "mt_act_bwd")
+    _check(_m.act_bwd(_act_code(act), z, dy, dz, db, ACCUMULATE if accumulate else 0, workspace, stream),
+           "mt_act_bwd")
 
 
 def mse_loss_workspace(pred, target) -> int:
@@ -261,42 +259,24 @@ def mse_loss_workspace(pred, target) -> int:
 
 def mse_loss(pred, target, loss=None, dpred=None, workspace=None, stream=None) -> None:
     """loss = mean((pred - target)^2) (1-element tensor), dpred = 2 (pred - target) / N."""
-    ds = [desc(t) for t in (pred, target, loss, dpred)]
-    ptr, nbytes = _ws(workspace)
-    _check(lib.mt_mse_loss(*[_ref(d) for d in ds], ptr, nbytes, _stream(stream)), "mt_mse_loss")
-
-
-def _desc_array(ts):
-    arr = (MtTensor * max(1, len(ts)))()
-    for i, t in enumerate(ts):
-        arr[i] = desc(t)
-    return arr
+    _check(_m.mse_loss(pred, target, loss, dpred, workspace, stream), "mt_mse_loss")
 
 
 def sgd_step(params, grads, velocity, lr, momentum=0.0, weight_decay=0.0, stream=None) -> None:
     """In place: v = momentum v + g + weight_decay p; p -= lr v (lists of tensors)."""
-    n = len(params)
-    assert len(grads) == n and len(velocity) == n
-    _check(lib.mt_sgd_step(n, _desc_array(params), _desc_array(grads), _desc_array(velocity),
-                           lr, momentum, weight_decay, _stream(stream)), "mt_sgd_step")
+    _check(_m.sgd_step(params, grads, velocity, lr, momentum, weight_decay, stream), "mt_sgd_step")
 
 
 def adam_step(params, grads, exp_avg, exp_avg_sq, lr, beta1, beta2, eps, step,
               stream=None) -> None:
     """In place Adam update at step `step` (>= 1) with bias-corrected moments."""
-    n = len(params)
-    assert len(grads) == n and len(exp_avg) == n and len(exp_avg_sq) == n
-    _check(lib.mt_adam_step(n, _desc_array(params), _desc_array(grads), _desc_array(exp_avg),
-                            _desc_array(exp_avg_sq), lr, beta1, beta2, eps, int(step),
-                            _stream(stream)), "mt_adam_step")
+    _check(_m.adam_step(params, grads, exp_avg, exp_avg_sq, lr, beta1, beta2, eps, step, stream),
+           "mt_adam_step")
 
 
 def rmsprop_step(params, grads, sq_avg, lr, alpha, eps, stream=None) -> None:
     """In place: v = alpha v + (1 - alpha) g^2; p -= lr g / sqrt(v + eps)."""
-    n = len(params)
-    assert len(grads) == n and len(sq_avg) == n
-    _check(lib.mt_rmsprop_step(n, _desc_array(params), _desc_array(grads), _desc_array(sq_avg),
-                               lr, alpha, eps, _stream(stream)), "mt_rmsprop_step")
+    _check(_m.rmsprop_step(params, grads, sq_avg, lr, alpha, eps, stream), "mt_rmsprop_step")
 
 
 def _pair(v):
@@ -314,11 +294,7 @@ def conv2d_fwd_workspace(x, w, b, y, stride=1, padding=0) -> int:
 
 def conv2d_fwd(x, w, b, y, stride=1, padding=0, workspace=None, stream=None) -> None:
     """y = conv2d(x, w) + b (Eq. (6)); y channels-last [N, CO, Ho, Wo]."""
-    st, pd = _pair(stride), _pair(padding)
-    ds = [desc(t) for t in (x, w, b, y)]
-    ptr, nbytes = _ws(workspace)
-    _check(lib.mt_conv2d_fwd(*[_ref(d) for d in ds], *st, *pd, ptr, nbytes, _stream(stream)),
-           "mt_conv2d_fwd")
+    _check(_m.conv2d_fwd(x, w, b, y, *_pair(stride), *_pair(padding), workspace, stream), "mt_conv2d_fwd")
 
 
 def conv2d_bwd_workspace(x, w, dy, dx=None, dw=None, db=None, stride=1, padding=0) -> int:
@@ -334,12 +310,9 @@ def conv2d_bwd(x, w, dy, dx=None, dw=None, db=None, stride=1, padding=0, accumul
                workspace=None, reuse_unfold=False, stream=None) -> None:
     """Pullbacks of conv2d: dx, dw, db (None skips one). reuse_unfold: the
     workspace still holds the forward's unfolded input."""
-    st, pd = _pair(stride), _pair(padding)
-    ds = [desc(t) for t in (x, w, dy, dx, dw, db)]
-    ptr, nbytes = _ws(workspace)
     flags = (ACCUMULATE if accumulate else 0) | (CONV_REUSE_UNFOLD if reuse_unfold else 0)
-    _check(lib.mt_conv2d_bwd(*[_ref(d) for d in ds], *st, *pd, flags, ptr, nbytes,
-                             _stream(stream)), "mt_conv2d_bwd")
+    _check(_m.conv2d_bwd(x, w, dy, dx, dw, db, *_pair(stride), *_pair(padding), flags, workspace, stream),
+           "mt_conv2d_bwd")
 
 
 def _shape_call(fn, a, b, where):

@@ -2,7 +2,8 @@
 
 Every HIP source is compiled for gfx950 with packed-fp32 instruction
 selection disabled; the host sources go through the same driver. The result
-sits next to this file, where ``binding`` loads it.
+sits next to this file, where ``binding`` loads it, with the binding's own
+native module beside it.
 """
 from __future__ import annotations
 
@@ -10,6 +11,7 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -38,6 +40,18 @@ def _compile(src: str, objdir: str, extra: list[str], tag: str = "") -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    """The native half of binding.py: a CPython module, host code only."""
+    out = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+    tmp = out + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall",
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pymarshal.cpp"), "-o", tmp, "-ldl"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, out)
+
+
 def build(extra: list[str] | None = None, verbose: bool = False) -> str:
     extra = list(extra or [])
     objdir = os.path.join(HERE, "_build")
@@ -50,6 +64,7 @@ def build(extra: list[str] | None = None, verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, OUT)
+    _build_marshal()
     if verbose:
         print(f"built {OUT}")
     return OUT
