@@ -385,10 +385,11 @@ mt_status mt_matmul_shape(int32_t na, const int64_t* a, int32_t nb, const int64_
  * 1 = 256x128, 2 = 128x256, 3 = 128x128, 4 = 64x64, 5 = 256x256 with 8 waves;
  * tiles streamed straight into an LDS ring 6 = 256x256 (bf16: 8 waves),
  * 7 = 256x256 with 4 waves, 8 = 256x128, 9 = 128x256, 10 = 128x128,
- * 11 = 128x128 with 8 waves (bf16; fp32 as 10), 12 = 128x128 with 64-deep fp32
- * K-stages (bf16 maps it to 10), 13 = 256x192, 14 = 256x96 (K-contiguous B
+ * 11 = 128x128 with 8 waves (bf16; fp32 as 10), 12 = 128x128 with 64-deep
+ * K-stages, one block a CU (bf16: a four-stage ring), 13 = 256x192, 14 = 256x96 (K-contiguous B
  * only, else 8), 15 = 64x384 (13-15: fp32 operands without 16-byte aligned
- * rows only, else 8; bf16 10); fp32 operands that do not allow 16-byte loads
+ * rows only, else 8; bf16 10), 16 = 64x64, 17 = 32x32, 18 = 16x16 for small
+ * products, their waves sharing the contraction); fp32 operands that do not allow 16-byte loads
  * run on tiles 6, 8, 9, 10 and 13-15 with 4-byte lanes (11 and 12 map to 10),
  * else at 128x128 or 64x64; bf16 ones at 128x128 or 64x64); "vec1"
  * (1 = force the narrow-load kernels); "splits" (0..4096, split-K count for

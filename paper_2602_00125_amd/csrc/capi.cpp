@@ -190,10 +190,10 @@ int choose_cfg_aligned(int64_t M, int64_t N, int64_t batch, int64_t stages, bool
   // the 4-wave form (the 8-wave one is 3% slower on dX and dW there)
   const int mid = vec ? (bf16 ? mt::kCfgDma128x128 : mt::kCfgDma128x128w8)
                       : (bf16 ? mt::kCfg128x128 : mt::kCfgDma128x128);
-  // up to one tile per CU, fp32 with 16-byte loads: the 8-wave form at BK =
-  // 64 (one block per CU, half as many stages and barriers; on 4096 x 1024 x
-  // 1024: Y +1%, dX +2%, dW +5% split four ways against eight)
-  const int small = vec && !bf16 ? mt::kCfgDma128x128k64 : mid;
+  // up to one tile per CU, 16-byte loads: fp32 at BK = 64 (half as many stages
+  // and barriers), bf16 with a ring of four stages (2048^3: 32.0 -> 26.6 us a
+  // product; 2048 x 1536 x 1000: 20.4 / 25.9 / 26.1 -> 17.9 / 24.1 / 23.9)
+  const int small = vec ? mt::kCfgDma128x128k64 : mid;
   const int64_t t128 = tiles(128, 128);
   if (t128 >= 128) return t128 <= 256 ? small : mid;
   if (can_split && t128 * std::min<int64_t>(16, stages / 8) >= 256) {
@@ -314,8 +314,8 @@ size_t plan_gemm(GemmCall& g, bool may_split) {
                        g.vec, p.K, p.red_count);
   // the gathering convolution kernels exist on the DMA tiles 256x256 and 128x128
   if (g.conv && !mt::gemm_conv_cfg(g.cfg)) g.cfg = mt::kCfgDma128x128w8;
-  // the BK = 64 128x128 tile exists for fp32 with 16-byte lanes only
-  if (g.cfg == mt::kCfgDma128x128k64 && (g.bf16 || !g.vec))
+  // the one-block-a-CU 128x128 tile exists with 16-byte lanes only
+  if (g.cfg == mt::kCfgDma128x128k64 && !g.vec)
     g.cfg = g.bf16 ? mt::kCfgDma128x128 : mt::kCfgDma128x128w8;
   // the 256x192, 256x96 and 64x384 tiles exist for fp32 with 4-byte lanes
   // only, 256x96 with a K-contiguous B only
@@ -440,7 +440,7 @@ double ring_time(const GemmCall& g) {
       case mt::kCfgDma256x256: case mt::kCfgDma256x256w4: per = g.bf16 ? 1.8 : 4.8; break;
       case mt::kCfgDma256x128: case mt::kCfgDma128x256: case mt::kCfg256x128: case mt::kCfg128x256:
         per = g.bf16 ? 0.6 : 1.4; break;
-      case mt::kCfgDma128x128k64: per = 2.9; break;
+      case mt::kCfgDma128x128k64: per = g.bf16 ? 0.6 : 2.9; break;
       case mt::kCfgDma256x96: case mt::kCfgDma64x384: per = 0.85; break;
       default: per = g.bf16 ? 0.95 : 1.45; break;
     }

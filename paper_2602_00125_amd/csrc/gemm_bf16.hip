@@ -70,6 +70,10 @@ static hipError_t launch_layout(const GemmParams& p, int cfg, hipStream_t stream
       case kCfgDma256x128: return launch_dma<A_KC, B_KC, 256, 128, 32, 2, 2, 3, 2>(p, stream);
       case kCfgDma128x256: return launch_dma<A_KC, B_KC, 128, 256, 32, 2, 2, 3, 2>(p, stream);
       case kCfgDma128x128: return launch_dma<A_KC, B_KC, 128, 128, 64, 2, 2, 2, 2>(p, stream);
+      // a block a CU at most: four stages in the ring, three loads deep, where
+      // two blocks a CU of two stages each would be one (a stage is 0.25 us of
+      // matrix work and about 1 us of load latency)
+      case kCfgDma128x128k64: return launch_dma<A_KC, B_KC, 128, 128, 64, 2, 2, 4, 1>(p, stream);
       case kCfgDma128x128w8: return launch_dma<A_KC, B_KC, 128, 128, 64, 4, 2, 2, 4>(p, stream);
       case kCfg256x128: return launch_bf16<A_KC, B_KC, 256, 128, 32, 2, 2, VEC, 2>(p, stream);
       case kCfg128x256: return launch_bf16<A_KC, B_KC, 128, 256, 32, 2, 2, VEC, 2>(p, stream);

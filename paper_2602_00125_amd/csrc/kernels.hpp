@@ -26,7 +26,7 @@ enum GemmCfg {
   kCfgDma128x256 = 9,    // 128x256, likewise
   kCfgDma128x128 = 10,   // 128x128, 4 waves, BK = 32 / 64, 2-stage ring (64 KB), 2 blocks per CU
   kCfgDma128x128w8 = 11, // the same tile with 8 waves of 32x64 (bf16; fp32 as 4 waves)
-  kCfgDma128x128k64 = 12, // fp32 only: 128x128, 4 waves, BK = 64, 2-stage ring (128 KB), 1 block per CU
+  kCfgDma128x128k64 = 12, // 128x128, 4 waves, BK = 64, 128 KB, 1 block per CU: fp32 2 stages, bf16 4
   // fp32 operands without 16-byte aligned rows (4-byte lanes), tiles shaped
   // for dimensions just past a multiple of 128 or 256 (every wave 64x96):
   kCfgDma256x192 = 13,   // 8 waves, BK = 16, 4-stage ring (112 KB), 1 block per CU
