@@ -165,8 +165,8 @@ int choose_cfg_aligned(int64_t M, int64_t N, int64_t batch, int64_t stages, bool
   const bool wide_waste = !bf16 && M > 0 && N > 0 && tiles(256, 256) < 1024 && used(256, 256) < 0.85;
   // Large products (measured on 8192^3 fp32 and 16384x8192x8192 bf16, all
   // three layouts): the 256x256 tile whose operands stream straight into a
-  // two-stage LDS ring, one block of 8 waves per CU, once there are enough
-  // tiles to fill every CU.
+  // two-stage LDS ring, one block per CU (fp32 of 4 waves, bf16 of 8), once
+  // there are enough tiles to fill every CU.
   // bf16 with both operands K-contiguous (the forward layout) takes the
   // 4-wave form, 128x128 accumulators per wave (measured on 16384 x 8192 x
   // 8192: NT 1.889 -> 1.810 ms; NN 1.809 -> 1.828 and TN 1.788 -> 1.858 ms,
@@ -183,11 +183,11 @@ int choose_cfg_aligned(int64_t M, int64_t N, int64_t batch, int64_t stages, bool
       return mt::kCfgDma256x256;
   }
   if (tiles(128, 256) >= 512) return N >= M ? mt::kCfg128x256 : mt::kCfg256x128;
-  // mid-size products: the 128x128 tile streamed into an LDS ring, two blocks
-  // per CU (measured on 4096 x 1024 x 1024: 96-106 TFLOP/s fp32 against 88-93
-  // for the register-staged 128x128 tile); fp32 with 16-byte loads takes its
-  // 8-wave form (98-114: one block per CU still has two waves per SIMD), bf16
-  // the 4-wave form (the 8-wave one is 3% slower on dX and dW there)
+  // mid-size products: the 128x128 tile of 4 waves streamed into an LDS ring,
+  // two blocks per CU (measured on 4096 x 1024 x 1024: bf16 255-392 TFLOP/s
+  // against 239-315 for the register-staged 128x128 tile, the 8-wave form 3%
+  // slower on dX and dW; fp32 56.5 us against 57.3 with 8 waves: its launch
+  // takes kCfgDma128x128w8 as the 4-wave tile)
   const int mid = vec ? (bf16 ? mt::kCfgDma128x128 : mt::kCfgDma128x128w8)
                       : (bf16 ? mt::kCfg128x128 : mt::kCfgDma128x128);
   // up to one tile per CU, 16-byte loads: fp32 at BK = 64 (half as many stages
@@ -430,7 +430,12 @@ double ring_time(const GemmCall& g) {
   const double stages = (double)p.stages_per_split;
   const double rounds = std::ceil(blocks / 256.0);
   double t;
-  if (g.cfg == mt::kCfg64x64) {
+  if (!g.bf16 && g.cfg == mt::kCfg128x128) {
+    // the nonlinearity's epilogue without 16-byte rows: 4-byte lanes and
+    // stores on the 128x128 ring tile (1001 x 2049 x 2047, 136 blocks: 142 us;
+    // 4001 x 2001 x 1001, 512: 130; 4095^3: 814; the 64x64 small tile 114, 194, 1158)
+    t = rounds * (24.0 + stages * (blocks > 256 ? 1.4 : 2.1));
+  } else if (g.cfg == mt::kCfg64x64) {
     // four blocks a CU: 0.5 us (bf16 0.38) a stage until they fill it
     t = 3.5 + stages * (g.bf16 ? 0.38 : 0.5) * std::max(1.0, blocks / 640.0) * (g.vec ? 1.0 : g.bf16 ? 2.0 : 1.5);
   } else {

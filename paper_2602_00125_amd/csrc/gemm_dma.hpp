@@ -1,13 +1,14 @@
 // Matrix-core GEMM whose operand tiles travel from HBM straight into LDS
 // (buffer_load_dwordx4 ... lds), gfx950 only. Same contract and epilogue as
 // gemm_kernel.hpp (MiniTensor Sec. 3.1 Eq. (1), Sec. 3.2 Eq. (4), Sec. 3.3
-// Eq. (5)); used for 16-byte-aligned operands of large products.
+// Eq. (5)); used for large products: 16-byte-aligned operands of both types,
+// and fp32 ones of any alignment by 4-byte lanes.
 //
 // Why: the loads write LDS themselves, so no staging registers and no
 // ds_write instructions sit between HBM and the fragments. Tiles are
 // 256x256 with BK = 32 (fp32) or 64 (bf16), i.e. 64 KB per stage, and the
-// ring holds NS = 2 stages (128 KB of the 160 KB LDS): one stage is ~3 us of
-// fp32 or ~1 us of bf16 matrix work at 256x256, long enough for its
+// ring holds NS = 2 stages (128 KB of the 160 KB LDS): one stage is ~2.6 us
+// of fp32 or ~1 us of bf16 matrix work at 256x256, long enough for its
 // successor's loads to land, and the per-stage costs (barrier, first
 // fragment reads, load issue) are paid half as often as with BK = 16 / 32
 // in a deeper ring. The kernel accepts rings of 2 to 5 stages.

@@ -315,6 +315,7 @@ int gemm_tile_k(int cfg, bool bf16) {
   if (gemm_small_cfg(cfg)) return 32;
   if (cfg == kCfgDma128x128k64) return 64;
   if (cfg == kCfg256x256x64w8) return bf16 ? 64 : 32;
+  if (!bf16 && (cfg == kCfg256x256 || cfg == kCfg128x128)) return 32;  // as the ring tiles they run on
   if (cfg == kCfgDma256x256 || cfg == kCfgDma256x256w4 || cfg == kCfgDma128x128 ||
       cfg == kCfgDma128x128w8)
     return bf16 ? 64 : 32;

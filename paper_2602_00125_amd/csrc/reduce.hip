@@ -411,7 +411,7 @@ static bool reduce_is_inner(const ReducePlan& plan) {
 // Parts of the summed range: about 1024 blocks of 256 lanes where the outputs
 // alone give fewer, each part at least 16 elements a lane (32 x 128 x 4096
 // summed to 128 values: one wave an output 526 us, 8 parts of a block each
-// about 20 us).
+// 16 us).
 int reduce_parts(const ReducePlan& plan) {
   if (plan.nred == 0 || plan.keep_count == 0) return 1;
   const int64_t elems = plan.keep_count * plan.red_count;
