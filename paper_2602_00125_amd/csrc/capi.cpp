@@ -393,9 +393,11 @@ size_t plan_gemm(GemmCall& g, bool may_split) {
                   : tiles_bytes;
 }
 
-// ---- small products (gemm_small.hpp) or ring tiles: an estimate of each, in
-// us, fitted to products of 1 to 8192 rows, columns and terms on the box
-// (within about 30%; it only has to rank them).
+// ---- small products (gemm_small.hpp) or the other tiles: an estimate of each,
+// in us, fitted by least squares to 252 products of 64 to 4096 rows, columns
+// and terms of both types, all layouts, aligned and not (the small tiles
+// within 15% for fp32 and 30% for bf16, the 128x128 ones 13%, 64x64 30%; it
+// only has to rank them).
 
 // A small tile's time: a launch, and per round of 256 blocks (one a CU) what a
 // block costs by itself and per K-step of a wave; `vmax` of the slowest block.
@@ -405,19 +407,20 @@ struct SmallEst {
 };
 SmallEst small_est(const GemmCall& g, int cfg) {
   const mt::GemmParams& p = g.p;
-  // launch, block, K-step: fp32 64x64 / 32x32 / 16x16 (1024^3 24 us, 512^3 9.4,
-  // 256^3 5.6), bf16 about half (12, 5.6, 4.5)
-  static const double f32[3][3] = {{3.0, 4.5, 3.4}, {2.5, 3.2, 1.9}, {1.5, 2.2, 2.1}};
-  static const double b16[3][3] = {{2.5, 2.5, 1.75}, {2.0, 1.6, 0.95}, {1.5, 1.5, 1.05}};
+  // launch, block, K-step, K tail (in K-steps: it is read element by element),
+  // and what a K-step costs more when both operands are contiguous along k
+  // (more lines a load), and without 16-byte rows; 64x64 / 32x32 / 16x16
+  static const double f32[3][6] = {{1.6, 5.8, 2.7, 0.5, 1.29, 1.04}, {1.8, 2.9, 1.6, 0.4, 1.21, 1.04},
+                                   {1.7, 2.3, 1.5, 0.3, 1.14, 1.10}};
+  static const double b16[3][6] = {{1.1, 3.2, 1.1, 0.9, 1.5, 1.24}, {1.8, 1.75, 0.65, 1.15, 1.36, 1.26},
+                                   {2.0, 1.8, 0.87, 0.7, 1.0, 1.24}};
   const int i = cfg - mt::kCfgSmall64;
   const double* c = g.bf16 ? b16[i] : f32[i];
   const int64_t t = mt::gemm_tile_m(cfg), waves = cfg == mt::kCfgSmall16 ? 16 : 8;
   const int64_t tiles = cdiv(p.M, t) * cdiv(p.N, t) * p.keep_count * p.splits;
-  // an operand contiguous along k costs more lines per load; a K tail is read
-  // element by element
-  const double step = c[2] * (g.a_kc && g.b_kc ? 1.0 : 0.85) * (g.vec ? 1.0 : 1.15);
+  const double step = c[2] * (g.a_kc && g.b_kc ? c[4] : 1.0) * (g.vec ? 1.0 : c[5]);
   const int64_t whole = p.K / 32 * p.red_count, tails = p.K % 32 ? p.red_count : 0;
-  const double steps = (double)cdiv(cdiv(whole, p.splits), waves) + 1.5 * (double)cdiv(cdiv(tails, p.splits), waves);
+  const double steps = (double)cdiv(cdiv(whole, p.splits), waves) + c[3] * (double)cdiv(cdiv(tails, p.splits), waves);
   return {c[0], c[1] + steps * step, tiles};
 }
 double small_time(const SmallEst& e) { return e.launch + e.block * (double)cdiv(e.tiles, 256); }
@@ -429,29 +432,33 @@ double ring_time(const GemmCall& g) {
                                  p.keep_count * p.splits);
   const double stages = (double)p.stages_per_split;
   const double rounds = std::ceil(blocks / 256.0);
-  double t;
-  if (!g.bf16 && g.cfg == mt::kCfg128x128) {
-    // the nonlinearity's epilogue without 16-byte rows: 4-byte lanes and
-    // stores on the 128x128 ring tile (1001 x 2049 x 2047, 136 blocks: 142 us;
-    // 4001 x 2001 x 1001, 512: 130; 4095^3: 814; the 64x64 small tile 114, 194, 1158)
-    t = rounds * (24.0 + stages * (blocks > 256 ? 1.4 : 2.1));
-  } else if (g.cfg == mt::kCfg64x64) {
-    // four blocks a CU: 0.5 us (bf16 0.38) a stage until they fill it
-    t = 3.5 + stages * (g.bf16 ? 0.38 : 0.5) * std::max(1.0, blocks / 640.0) * (g.vec ? 1.0 : g.bf16 ? 2.0 : 1.5);
-  } else {
-    // us per stage of one block alone on its CU
-    double per;
-    switch (g.cfg) {
-      case mt::kCfgDma256x256: case mt::kCfgDma256x256w4: per = g.bf16 ? 1.8 : 4.8; break;
-      case mt::kCfgDma256x128: case mt::kCfgDma128x256: case mt::kCfg256x128: case mt::kCfg128x256:
-        per = g.bf16 ? 0.6 : 1.4; break;
-      case mt::kCfgDma128x128k64: per = g.bf16 ? 0.6 : 2.9; break;
-      case mt::kCfgDma256x96: case mt::kCfgDma64x384: per = 0.85; break;
-      default: per = g.bf16 ? 0.95 : 1.45; break;
-    }
-    if (g.bf16) per *= std::min(1.0, 0.55 + 0.45 * blocks / 256.0);
-    t = 5.0 + rounds * (4.0 + stages * per * (g.vec ? 1.0 : g.bf16 ? 3.0 : 1.3));
+  const double act = p.act || p.z ? 1.0 : 0.0;  // the nonlinearity's epilogue
+  const double mb = (double)(p.splits + 1) * (double)(p.M * p.N * p.keep_count) * 1e-6;
+  const bool cut = p.splits > 1;
+  if (g.cfg == mt::kCfg64x64) {
+    // four blocks a CU, whose stages slow each other down from about 320 on
+    const double slow = std::max(1.0, blocks / 330.0), tail = act * 1.6 * std::ceil(blocks / 1024.0);
+    if (!g.bf16) return 6.4 + stages * 0.458 * (g.vec ? 1.0 : 1.29) * slow + tail + (cut ? 3.0 + 2.8 * mb : 0.0);
+    return (g.vec ? 4.8 : 7.9) + stages * (g.vec ? 0.29 : 0.53) * slow + tail + (cut ? 5.5 + mb : 0.0);
   }
+  if (!g.conv && (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8)) {
+    if (!g.bf16)
+      return 7.5 + rounds * (act * (g.vec ? 7.9 : 20.7) + stages * (g.vec ? 1.43 : 1.65)) + (cut ? 3.0 + 0.75 * mb : 0.0);
+    if (g.vec) return 5.9 + rounds * (1.5 + 7.0 * act + stages * 0.53) + (cut ? 1.6 + 0.8 * mb : 0.0);
+    return 6.4 + rounds * (7.0 + 11.3 * act) + stages * 1.3 * std::max(1.0, blocks / 550.0) + (cut ? 1.6 + 0.8 * mb : 0.0);
+  }
+  // us per stage of one block alone on its CU
+  double per;
+  switch (g.cfg) {
+    case mt::kCfgDma256x256: case mt::kCfgDma256x256w4: per = g.bf16 ? 1.8 : 4.8; break;
+    case mt::kCfgDma256x128: case mt::kCfgDma128x256: case mt::kCfg256x128: case mt::kCfg128x256:
+      per = g.bf16 ? 0.6 : 1.4; break;
+    case mt::kCfgDma128x128k64: per = g.bf16 ? 0.6 : 2.9; break;
+    case mt::kCfgDma256x96: case mt::kCfgDma64x384: per = 0.85; break;
+    default: per = g.bf16 ? 0.95 : 1.45; break;
+  }
+  if (g.bf16) per *= std::min(1.0, 0.55 + 0.45 * blocks / 256.0);
+  double t = 5.0 + rounds * (4.0 + stages * per * (g.vec ? 1.0 : g.bf16 ? 3.0 : 1.3));
   if (p.splits > 1) t += 4.0 + (double)(p.splits + 1) * (double)(p.M * p.N * p.keep_count) * 1e-6;
   return t;
 }
@@ -472,7 +479,7 @@ int choose_small(const GemmCall& planned, double* time) {
   g.p.splits = 1;
   for (int cfg : {mt::kCfgSmall64, mt::kCfgSmall32, mt::kCfgSmall16}) {
     const double t = small_time(small_est(g, cfg));
-    if (t < 0.9 * *time) {
+    if (t < 0.95 * *time) {
       *time = t;
       best = cfg;
     }
@@ -531,6 +538,22 @@ mt_status launch_gemm(GemmCall& g, hipStream_t stream, void* ws, size_t ws_bytes
     g = asked;
     g.cfg = small;
     need = plan_gemm(g, ws != nullptr);
+  } else if (g_force_cfg < 0 && !g.conv && !p.colsum &&
+             (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8)) {
+    // 64x64 tiles where a few 128x128 ones have short contractions (2432 x 832
+    // x 128 with GELU: 22.9 us against 13.5)
+    GemmCall c = asked;
+    c.cfg = mt::kCfg64x64;
+    size_t n = plan_gemm(c, ws != nullptr);
+    if (n > ws_bytes) {
+      c = asked;
+      c.cfg = mt::kCfg64x64;
+      n = plan_gemm(c, false);
+    }
+    if (ring_time(c) < 0.95 * est) {
+      g = c;
+      need = n;
+    }
   }
   if (g.sk && need > ws_bytes) g.sk = 0;  // no room for the partial tiles: one tile per block
   if (g.sk) {
