@@ -534,7 +534,9 @@ mt_status launch_gemm(GemmCall& g, hipStream_t stream, void* ws, size_t ws_bytes
   }
   // (the workspace queries go by the ring tiles' plan, whatever runs)
   double est;
-  if (const int small = choose_small(g, &est); small >= 0) {
+  if (mt::relu_saves_z(p)) {
+    // one order of its sums: the tile that was asked for
+  } else if (const int small = choose_small(g, &est); small >= 0) {
     g = asked;
     g.cfg = small;
     need = plan_gemm(g, ws != nullptr);

@@ -542,6 +542,40 @@ struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
   }
 };
 
+// fp32 products on the fp32 instructions, K-contiguous operands: the sums of a
+// ReLU layer that saves its pre-activation (see relu_saves_z). A k-step is a
+// group of 8 k; within it, MFMA step j (0..3) takes k = 8g + 4h + j for lane
+// half h (one 16-byte read of a tile row feeds 4 steps).
+template <int TM, int TN, int BK, int BM, int BN>
+struct DmaMmaF32 {
+  static constexpr int KSTEPS = BK / 8;
+  static constexpr bool ROW_PERM = false;
+  static constexpr int CHUNKS = 4;  // chunk j: MFMA step j of every tile
+  struct Frags {
+    float a[4][TM], b[4][TN];
+  };
+  template <int BMN, int N>
+  static __device__ __forceinline__ void frag(const char* S, int mn0, int g, int lane, float (&f)[4][N], int i) {
+    const f32x4 v = *(const f32x4*)(S + DmaTile<4, true, BMN, BK>::addr(mn0 + (lane & 31), 8 * g + 4 * (lane >> 5)));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[j][i] = v[j];
+  }
+  static __device__ __forceinline__ void load(const char* As, const char* Bs, int am, int bn, int lane, int g,
+                                              Frags& f) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) frag<BM, TM>(As, am + i * 32, g, lane, f.a, i);
+#pragma unroll
+    for (int i = 0; i < TN; ++i) frag<BN, TN>(Bs, bn + i * 32, g, lane, f.b, i);
+  }
+  static __device__ __forceinline__ void compute_chunk(const Frags& f, f32x16 (&acc)[TM][TN], int j) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int q = 0; q < TN; ++q)
+        acc[i][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.b[j][q], f.a[j][i], acc[i][q], 0, 0, 0);
+  }
+};
+
 // bf16: a k-step covers 16 k; lane half h supplies k = 16s + 8h + 0..7.
 template <bool A_KC, bool B_KC, int TM, int TN, int BK, int BM, int BN>
 struct DmaMma<__bf16, A_KC, B_KC, TM, TN, BK, BM, BN> {
@@ -616,10 +650,11 @@ struct DmaMma<__bf16, A_KC, B_KC, TM, TN, BK, BM, BN> {
 
 // PERSIST: the grid holds one block per CU and block b computes the tiles
 // the plain grid's blocks b, b + gridDim.x, ... would (plain products only).
+// SPLIT (fp32): on the bf16 matrix cores (DmaMma<float>), else DmaMmaF32.
 template <typename T, bool A_KC, bool B_KC, int BM, int BN, int BK, int WGM, int WGN, int NS,
           int DMA_G0, int DMA_GS, bool KTAIL,
           int WAVES_PER_EU, bool EPI = false, int DMA_LANE = 16, bool VEC_C = true,
-          bool PERSIST = false>
+          bool PERSIST = false, bool SPLIT = true>
 __global__ __launch_bounds__(WGM * WGN * 64)
 __attribute__((amdgpu_waves_per_eu(WAVES_PER_EU, WAVES_PER_EU)))
 void gemm_dma_kernel(const GemmParams p) {
@@ -645,7 +680,7 @@ void conv_dma_kernel(const GemmParams p) {
   constexpr bool SK = false, sk_part = false;
   constexpr int64_t sk_t = 0, sk_ka = 0, sk_kb = 0;
   constexpr int sk_slot = 0;
-  constexpr bool PERSIST = false;
+  constexpr bool PERSIST = false, SPLIT = true;
 #include "gemm_dma_body.inc"
 }
 
@@ -682,7 +717,7 @@ void conv_dma_sk_kernel(const GemmParams p) {
   using T = float;
   constexpr bool A_KC = true, B_KC = CONV_ == 1, EPI = false, VEC_C = true, KTAIL = false;
   constexpr int DMA_G0 = 1, DMA_GS = 1, DMA_LANE = 16, CONV = CONV_;
-  constexpr bool SK = true, PERSIST = false;
+  constexpr bool SK = true, PERSIST = false, SPLIT = true;
   const int64_t ks_all = (p.K + BK - 1) / BK;
   const int64_t U = (int64_t)p.tiles_m * p.tiles_n * ks_all, G = gridDim.x;
   const int64_t u_end = ((int64_t)blockIdx.x + 1) * U / G;
@@ -734,7 +769,7 @@ void conv_dgrad_phases_kernel(const GemmParams p0, const ConvPhases tab) {
   p.cg.ho_shift = f.ho_shift;
   const int64_t sk_t = (int64_t)blockIdx.x - tab.tile0[k];
   const int64_t sk_ka = 0, sk_kb = (f.K + BK - 1) / BK;
-  constexpr bool PERSIST = false;
+  constexpr bool PERSIST = false, SPLIT = true;
 #include "gemm_dma_body.inc"
 }
 

@@ -37,7 +37,7 @@ static hipError_t launch_f32(const GemmParams& p, hipStream_t stream) {
 }
 
 template <bool A_KC, bool B_KC, int BM, int BN, int BK, int WGM, int WGN, int NS, int WPE,
-          bool EPI = false, int LANE = 16, bool VEC_C = true>
+          bool EPI = false, int LANE = 16, bool VEC_C = true, bool SPLIT = true>
 static hipError_t launch_dma(const GemmParams& p, hipStream_t stream) {
   GemmParams q = p;
   q.tiles_m = (int32_t)((p.M + BM - 1) / BM);
@@ -56,10 +56,10 @@ static hipError_t launch_dma(const GemmParams& p, hipStream_t stream) {
   }
   // the per-load K-tail test only where K is not a whole number of stages
   if (p.K % BK != 0)
-    hipLaunchKernelGGL((gemm::gemm_dma_kernel<float, A_KC, B_KC, BM, BN, BK, WGM, WGN, NS, 1, 1, true, WPE, EPI, LANE, VEC_C>),
+    hipLaunchKernelGGL((gemm::gemm_dma_kernel<float, A_KC, B_KC, BM, BN, BK, WGM, WGN, NS, 1, 1, true, WPE, EPI, LANE, VEC_C, false, SPLIT>),
                        dim3((unsigned)blocks), dim3(WGM * WGN * 64), 0, stream, q);
   else
-    hipLaunchKernelGGL((gemm::gemm_dma_kernel<float, A_KC, B_KC, BM, BN, BK, WGM, WGN, NS, 1, 1, false, WPE, EPI, LANE, VEC_C>),
+    hipLaunchKernelGGL((gemm::gemm_dma_kernel<float, A_KC, B_KC, BM, BN, BK, WGM, WGN, NS, 1, 1, false, WPE, EPI, LANE, VEC_C, false, SPLIT>),
                        dim3((unsigned)blocks), dim3(WGM * WGN * 64), 0, stream, q);
   return hipGetLastError();
 }
@@ -117,7 +117,24 @@ static hipError_t launch_epi(const GemmParams& p, bool vec, int cfg, hipStream_t
   return launch_dma<true, true, 128, 128, 32, 2, 2, 2, 2, true>(p, stream);
 }
 
+// A ReLU layer that saves z (relu_saves_z): the fp32 instructions, on the
+// 256x256 tile of 8 waves, the 128x128 one or the 64x64 register-staged one.
+static hipError_t launch_relu_z(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
+  if (cfg == kCfg64x64)
+    return vec ? launch_f32<true, true, 64, 64, 16, 2, 2, 4, 4, true>(p, stream)
+               : launch_f32<true, true, 64, 64, 16, 2, 2, 1, 4, true>(p, stream);
+  if (!vec) {
+    GemmParams q = p;  // (never split: the stages of this tile are 16 deep)
+    q.stages_per_split = p.K > 0 ? (p.K + 15) / 16 : 1;
+    return launch_f32<true, true, 128, 128, 16, 2, 2, 1, 2, true>(q, stream);
+  }
+  if (cfg == kCfgDma256x256)
+    return launch_dma<true, true, 256, 256, 32, 2, 4, 2, 2, true, 16, true, false>(p, stream);
+  return launch_dma<true, true, 128, 128, 32, 2, 2, 2, 2, true, 16, true, false>(p, stream);
+}
+
 hipError_t gemm_f32_nt(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
+  if (relu_saves_z(p)) return launch_relu_z(p, vec, cfg, stream);
   if (p.act || p.z) return launch_epi(p, vec, cfg, stream);
   return launch_layout<true, true>(p, vec, cfg, stream);
 }
