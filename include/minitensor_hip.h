@@ -34,12 +34,12 @@
  *   - Outputs must not overlap any input or each other (MT_ERR_ALIAS).
  *   - Results are deterministic: no floating-point atomics are used, so the
  *     same call on the same inputs returns bit-identical outputs.
- *   - Floating point: products of fp32 operands are summed in fp32; larger
- *     ones run on the bf16 matrix cores with every value split exactly into
- *     three bf16 parts (six v_mfma_f32_32x32x16_bf16 per 16 terms; measured
- *     nearer the exact sums than fp32 instructions), falling back to
- *     v_mfma_f32_32x32x2_f32 for tiles the split does not serve (infinities,
- *     NaN, values next to the largest float, rows of tiny values). bf16 operands are multiplied
+ *   - Floating point: products of fp32 operands are summed in fp32. Larger
+ *     ones run on the bf16 matrix cores, every value split exactly into three
+ *     bf16 parts (six v_mfma_f32_32x32x16_bf16 per 16 terms; products below
+ *     2^-24 of a term are left out). Tiles whose results are not finite that
+ *     way (infinities, NaN, values from 2^104 and sums from 2^80 on) are
+ *     computed by v_mfma_f32_32x32x2_f32 instead. bf16 operands are multiplied
  *     exactly and accumulated in fp32 (v_mfma_f32_32x32x16_bf16). Every
  *     output, bias and bias gradient is fp32.
  */

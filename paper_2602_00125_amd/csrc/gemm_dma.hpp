@@ -358,9 +358,11 @@ struct ConvGatherB {
 template <typename T, bool A_KC, bool B_KC, int TM, int TN, int BK, int BM, int BN>
 struct DmaMma;
 
-// fp32 products on the bf16 matrix cores, "X6". Every fp32 value is the sum of
-// three bf16 values of 8 significand bits each, x = h + m + l (h = x rounded
-// to bf16, m and l the same of what is left; exact down to 2^-134), so
+// fp32 products on the bf16 matrix cores, "X6" (three parts and six products a
+// pair: G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations", 2019).
+// Every fp32 value is the sum of three bf16 values of 8 significand bits each,
+// x = h + m + l (h = x rounded to bf16, m and l the same of what is left), so
 //   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + terms below 2^-24 |a b|,
 // six v_mfma_f32_32x32x16_bf16 per 16 k, exact products summed in fp32, small
 // terms first. An accumulator is rounded 6 times per 16 k where the fp32
@@ -375,15 +377,23 @@ struct DmaMma;
 // contractions) therefore negate B in every other run, and the runs' losses
 // cancel (0.95e-6).
 //
-// Not every input may be split: an infinite or NaN value gives NaN parts, one
-// within 2^-9 of the largest float rounds to an infinite h, and a row whose
-// values are all tiny loses its l (bf16 ends at 2^-133). The block therefore
-// checks its accumulators (every one finite) and that each row of A and
-// column of B is zero or holds a value of at least 2^-95 (parts lost below
-// 2^-126 are then under 2^-31 of it), and where either fails computes the
-// tile again with the fp32 instructions (plain_tile). The second check is the
-// OR of the h planes' bits: exponents below 32 leave the exponent's top three
-// bits clear, and one v_or3 takes four values.
+// bf16 ends at 2^-133 (2^-126 without subnormals), so the parts of a value
+// below 2^-110 would lose its last bits, and a small value beside a large one
+// in its row may still be all that a result is made of. Both operands are
+// therefore split scaled by 2^24 (X6_SCALE): the last bit of the smallest
+// subnormal float, 2^-149, becomes 2^-125, and the split of every finite value
+// is exact, in normal bf16 values. The accumulators hold 2^48 times the sums
+// and are scaled back before the epilogue (exactly, but for results below
+// 2^-126). What the scale takes at the top is seen in the results: a value
+// from 2^104 on, an infinity or a NaN has parts that are infinite or NaN, and
+// sums from 2^80 on may overflow, so the accumulators are not finite. The
+// block checks that, and computes such a tile again with the fp32
+// instructions (plain_tile).
+// (One multiplication a value. A check by row, which cannot see small values
+// beside large ones, was a quarter of an instruction: 8192^3 step 15.57 ms,
+// with the scale 16.09.)
+constexpr float X6_SCALE = 0x1p24f, X6_UNSCALE = 0x1p-48f;
+
 template <bool A_KC, bool B_KC, int TM, int TN, int BK, int BM, int BN>
 struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
   static constexpr int KSTEPS = BK / 16;
@@ -448,26 +458,21 @@ struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
       frag<A_KC, BM>(As, am + i * 32, ks, lane, f.a[i]);
     }
   }
-  // sign: 0, or the sign bit to split -x
-  static __device__ __forceinline__ Planes split(const float (&x)[8], uint32_t sign) {
-    float y[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = __uint_as_float(__float_as_uint(x[e]) ^ sign);
-    return split(y);
-  }
-  static __device__ __forceinline__ Planes split(const float (&x)[8]) {
+  // the parts of scale x
+  static __device__ __forceinline__ Planes split(const float (&x)[8], float scale) {
     // x - h as one v_dot2_f32_bf16 per value, h's register and its neighbour's
-    // against (-1, 0) or (0, -1): 7 instructions a pair where taking the
-    // halves apart and subtracting takes 11 (8192^3: 4.90 against 4.93 ms, and
-    // less power). Opaque: as an immediate the compiler would take the pair
-    // for the inline constant -1.0, which the instruction reads as (0, -1).
+    // against (-1, 0) or (0, -1): with the scale 9 instructions a pair where
+    // taking the halves apart and subtracting takes 13 (8192^3, without the
+    // scale: 4.90 against 4.93 ms, and less power). Opaque: as an immediate
+    // the compiler would take the pair for the inline constant -1.0, which the
+    // instruction reads as (0, -1).
     uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;
     __asm__("" : "+s"(c0), "+s"(c1));
     const bf16x2 n0 = __builtin_bit_cast(bf16x2, c0), n1 = __builtin_bit_cast(bf16x2, c1);
     Planes p;
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
-      const f32x2 v = {x[e], x[e + 1]};
+      const f32x2 v = {x[e] * scale, x[e + 1] * scale};
       const bf16x2 h = __builtin_convertvector(v, bf16x2);  // v_cvt_pk_bf16_f32, nearest even
       const f32x2 r = {__builtin_amdgcn_fdot2_f32_bf16(h, n0, v[0], false),
                        __builtin_amdgcn_fdot2_f32_bf16(h, n1, v[1], false)};
@@ -506,27 +511,6 @@ struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
       cs[i] += ((f.a[i][0] + f.a[i][1]) + (f.a[i][2] + f.a[i][3])) +
                ((f.a[i][4] + f.a[i][5]) + (f.a[i][6] + f.a[i][7]));
   }
-  // the bits of a row's (column's) h planes, ORed
-  static __device__ __forceinline__ void note(const Planes& x, uint32_t& bits) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 h = __builtin_bit_cast(u32x4, x.h);
-    bits |= h[0] | h[1];
-    bits |= h[2] | h[3];
-  }
-  // whether any of the lane's rows holds only values too small to split; the
-  // bits start over
-  template <int N>
-  static __device__ __forceinline__ bool any_tiny(uint32_t (&bits)[N]) {
-    bool bad = false;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      uint32_t t = bits[i] | (uint32_t)__shfl_xor((int)bits[i], 32);
-      t |= t >> 16;
-      bad |= (t & 0x7fffu) != 0 && (t & 0x7000u) == 0;
-      bits[i] = 0;
-    }
-    return bad;
-  }
   static __device__ __forceinline__ bool any_not_finite(const f32x16 (&acc)[TM][TN]) {
     float z[4] = {0.f, 0.f, 0.f, 0.f};  // 0 x finite = 0, 0 x (inf or NaN) = NaN
 #pragma unroll
@@ -539,6 +523,13 @@ struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
       }
     const float t = (z[0] + z[1]) + (z[2] + z[3]);
     return t != t;
+  }
+  // the sums the accumulators stand for
+  static __device__ __forceinline__ void unscale(f32x16 (&acc)[TM][TN], float by) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int q = 0; q < TN; ++q) acc[i][q] *= by;
   }
 };
 

@@ -15,8 +15,8 @@
 //
 // v_mfma_f32_16x16x32_bf16: lane l of the first (second) operand holds row
 // (column) l & 15, k group g = l >> 4. A K-step is 32 k, dealt to the groups by
-// small_k on both operands. fp32 values are split in three bf16 parts, six products a pair, with the same checks
-// as DmaMma<float>. An operand contiguous along m (n) instead is read T
+// small_k on both operands. fp32 values are split in three bf16 parts, six
+// products a pair, scaled as in DmaMma<float>. An operand contiguous along m (n) instead is read T
 // consecutive rows at a time (T tiles): tile i's row r is row T r + i.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "act.hpp"
+#include "gemm_dma.hpp"
 #include "gemm_kernel.hpp"
 #include "gemm_params.hpp"
 
@@ -48,14 +49,14 @@ struct SmallOperand<float> {
     bf16x8 h, m, l;
   };
   static __device__ __forceinline__ void set(Raw& r, int e, float v) { r.x[e] = v; }
-  static __device__ __forceinline__ Frag frag(const Raw& r, uint32_t& bits) {
+  static __device__ __forceinline__ Frag frag(const Raw& r) {
     uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;  // (-1, 0), (0, -1): see DmaMma<float>::split
     __asm__("" : "+s"(c0), "+s"(c1));
     const bf16x2 n0 = __builtin_bit_cast(bf16x2, c0), n1 = __builtin_bit_cast(bf16x2, c1);
     u32x4 h, m, l;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const f32x2 v = {r.x[2 * e], r.x[2 * e + 1]};
+      const f32x2 v = {r.x[2 * e] * X6_SCALE, r.x[2 * e + 1] * X6_SCALE};
       const bf16x2 hh = __builtin_convertvector(v, bf16x2);
       const f32x2 s = {__builtin_amdgcn_fdot2_f32_bf16(hh, n0, v[0], false),
                        __builtin_amdgcn_fdot2_f32_bf16(hh, n1, v[1], false)};
@@ -66,8 +67,6 @@ struct SmallOperand<float> {
       m[e] = __builtin_bit_cast(uint32_t, mm);
       l[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(q, bf16x2));
     }
-    bits |= h[0] | h[1];
-    bits |= h[2] | h[3];
     return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
   }
   template <int TN>
@@ -88,6 +87,7 @@ struct SmallOperand<float> {
     return ((r.x[0] + r.x[1]) + (r.x[2] + r.x[3])) + ((r.x[4] + r.x[5]) + (r.x[6] + r.x[7]));
   }
   static __device__ __forceinline__ float value(float v) { return v; }
+  static constexpr float UNSCALE = X6_UNSCALE;  // of the accumulators
 };
 
 template <>
@@ -100,13 +100,14 @@ struct SmallOperand<__bf16> {
     bf16x8 v;
   };
   static __device__ __forceinline__ void set(Raw& r, int e, unsigned short v) { r.x[e] = v; }
-  static __device__ __forceinline__ Frag frag(const Raw& r, uint32_t&) { return {__builtin_bit_cast(bf16x8, r.x)}; }
+  static __device__ __forceinline__ Frag frag(const Raw& r) { return {__builtin_bit_cast(bf16x8, r.x)}; }
   template <int TN>
   static __device__ __forceinline__ void mfma(const Frag& a, const Frag (&b)[TN], f32x4 (&acc)[TN]) {
 #pragma unroll
     for (int q = 0; q < TN; ++q)
       acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[q].v, a.v, acc[q], 0, 0, 0);
   }
+  static constexpr float UNSCALE = 1.f;
   static __device__ __forceinline__ float value(unsigned short v) { return __uint_as_float((uint32_t)v << 16); }
   static __device__ __forceinline__ float sum(const Raw& r) {
     float s = 0.f;
@@ -216,7 +217,7 @@ template <typename T, bool A_KC, bool B_KC, int TM, int TN, int WK, int DEPTH, b
 struct SmallGemm {
   static constexpr int BM = 16 * TM, BN = 16 * TN, NTHR = 64 * WK;
   static constexpr int PITCH = BN + 4;  // floats per LDS row of a partial tile
-  static constexpr int LDS_FLOATS = WK * BM * PITCH + WK * BM + WK * (BM + BN) + WK;
+  static constexpr int LDS_FLOATS = WK * BM * PITCH + WK * BM;
   using Op = SmallOperand<T>;
   using E = typename Op::Elem;
 
@@ -277,12 +278,9 @@ struct SmallGemm {
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int q = 0; q < TN; ++q) acc[i][q] = f32x4{};
-    uint32_t a_bits[TM], b_bits[TN];
     float cs[TM];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) a_bits[i] = 0, cs[i] = 0.f;
-#pragma unroll
-    for (int q = 0; q < TN; ++q) b_bits[q] = 0;
+    for (int i = 0; i < TM; ++i) cs[i] = 0.f;
     const bool cs_on = !A_KC && p.colsum != nullptr && n0 == 0;
     auto multiply = [&](const typename Op::Raw (&xa)[TM], const typename Op::Raw (&xb)[TN]) {
       if constexpr (!A_KC) {
@@ -293,10 +291,10 @@ struct SmallGemm {
       }
       typename Op::Frag fb[TN];
 #pragma unroll
-      for (int q = 0; q < TN; ++q) fb[q] = Op::frag(xb[q], b_bits[q]);
+      for (int q = 0; q < TN; ++q) fb[q] = Op::frag(xb[q]);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const typename Op::Frag fa = Op::frag(xa[i], a_bits[i]);
+        const typename Op::Frag fa = Op::frag(xa[i]);
         Op::mfma(fa, fb, acc[i]);
       }
     };
@@ -383,6 +381,10 @@ struct SmallGemm {
     // ---- the waves' partial tiles meet in LDS
     float* const part = lds + wave * BM * PITCH;
 #pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int q = 0; q < TN; ++q) acc[i][q] *= Op::UNSCALE;
+#pragma unroll
     for (int i = 0; i < TM; ++i) {
       float* row = part + (A_KC ? 16 * i + r16 : TM * r16 + i) * PITCH;
       if constexpr (B_KC || TN == 1) {
@@ -397,8 +399,6 @@ struct SmallGemm {
       }
     }
     float* const cs_part = lds + WK * BM * PITCH;
-    uint32_t* const seen = (uint32_t*)(cs_part + WK * BM);  // [wave][BM + BN]: bits of the rows and columns
-    int* const vote = (int*)(seen + WK * (BM + BN));        // [wave]
     if constexpr (!A_KC) {
       if (cs_on) {
 #pragma unroll
@@ -410,39 +410,7 @@ struct SmallGemm {
         }
       }
     }
-    // rows and columns of values too small to split (see DmaMma<float>)
-    auto tiny = [](uint32_t b) {
-      b |= b >> 16;
-      return (b & 0x7fffu) != 0 && (b & 0x7000u) == 0;
-    };
-    if constexpr (std::is_same_v<T, float>) {
-      bool bad = false;
-      auto note = [&](uint32_t b, int slot) {
-        b |= (uint32_t)__shfl_xor((int)b, 16);
-        b |= (uint32_t)__shfl_xor((int)b, 32);
-        bad |= tiny(b);
-        if (g == 0) seen[wave * (BM + BN) + slot] = b;
-      };
-#pragma unroll
-      for (int i = 0; i < TM; ++i) note(a_bits[i], A_KC ? 16 * i + r16 : TM * r16 + i);
-#pragma unroll
-      for (int q = 0; q < TN; ++q) note(b_bits[q], BM + (B_KC ? 16 * q + r16 : TN * r16 + q));
-      const int any = __any(bad);
-      if (lane == 0) vote[wave] = any;
-    }
     __syncthreads();
-    bool some_tiny = false;
-    if constexpr (std::is_same_v<T, float>) {
-      for (int w = 0; w < WK; ++w) some_tiny |= vote[w] != 0;
-      if (some_tiny) {
-        for (int c = tid; c < BM + BN; c += NTHR) {
-          uint32_t b = 0;
-          for (int w = 0; w < WK; ++w) b |= seen[w * (BM + BN) + c];
-          seen[c] = tiny(b) ? 1u : 0u;  // (only this thread reads or writes column c)
-        }
-        __syncthreads();
-      }
-    }
     const bool to_partial = p.splits > 1;
     if (cs_on) {
       for (int c = tid; c < BM; c += NTHR) {
@@ -472,7 +440,7 @@ struct SmallGemm {
         uint32_t again = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (v[e] * 0.f != 0.f || (some_tiny && (seen[mr] | seen[BM + nr + e]) != 0)) again |= 1u << e;
+          if (v[e] * 0.f != 0.f) again |= 1u << e;
         if (again) {
           // fp32 multiply-adds from memory for what the split does not serve (rare)
 #pragma unroll 1

@@ -10,6 +10,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2602_00125_amd import binding as b  # noqa: E402
+from test_gpu_split import KINDS, check, spoil  # noqa: E402
 DEV = "cuda:0"
 TILES = {16: 64, 17: 32, 18: 16}
 # every tile edge +-1 and short, whole, one-past and long contractions
@@ -99,9 +100,8 @@ def test_batched_and_summed(cfg, K):
 
 
 @pytest.mark.parametrize("cfg", [16, 17, 18])
-@pytest.mark.parametrize("kind", ["inf", "nan", "huge", "tiny_rows", "tiny_rows_big_other", "zero_rows"])
+@pytest.mark.parametrize("kind", KINDS)
 def test_values_the_split_does_not_serve(cfg, kind):
-    from test_gpu_split import check, spoil
     g = torch.Generator().manual_seed(cfg)
     M, N, K = 210, 70, 136
     x, w = spoil(torch.randn(M, K, generator=g), torch.randn(N, K, generator=g), kind)

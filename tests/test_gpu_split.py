@@ -1,8 +1,9 @@
 """fp32 products on the bf16 matrix cores split every value in three bf16 parts.
 
-What the split does not serve (infinities, NaN, values near the largest float,
-rows of tiny values) must come out as in fp32 arithmetic, and what it serves
-must be no further from the exact sums than fp32 accumulation is.
+What the split does not serve (infinities, NaN, values and sums near the
+largest float) must come out as in fp32 arithmetic, and what it serves must be
+no further from the exact sums than fp32 accumulation is: tiny values too,
+also beside ordinary ones that meet a zero.
 """
 from __future__ import annotations
 
@@ -18,7 +19,8 @@ DEV = "cuda:0"
 # 256x256, 128x128 (two depths), 256x128, 128x256 with 16-byte lanes; with
 # vec1 those and 256x192, 256x96, 64x384 with 4-byte lanes
 CFGS = [(c, 0) for c in (6, 8, 9, 10, 12)] + [(c, 1) for c in (6, 8, 9, 10, 13, 14, 15)]
-KINDS = ["inf", "nan", "huge", "tiny_rows", "tiny_rows_big_other", "zero_rows"]
+KINDS = ["inf", "nan", "huge", "tiny_rows", "tiny_rows_big_other", "zero_rows", "mixed", "mixed_cols",
+         "subnormal", "big_sums"]
 
 
 def spoil(x, w, kind):
@@ -35,6 +37,20 @@ def spoil(x, w, kind):
     elif kind == "tiny_rows_big_other":
         x *= 1e-36
         w *= 1e30
+    elif kind == "mixed":  # an ordinary value in every row meets a zero; the rest is tiny
+        x *= 1e-37
+        w *= 1e30
+        x[:, 0], w[:, 0] = 1.0, 0.0
+    elif kind == "mixed_cols":  # the other way round, other magnitudes in each row
+        w *= 10.0 ** -torch.linspace(30, 38, len(w))[:, None]
+        x *= 1e29
+        w[:, 7], x[:, 7] = -3.0, 0.0
+    elif kind == "subnormal":
+        x *= 1e-40
+        w *= 1e30
+    elif kind == "big_sums":  # finite, beyond the scaled accumulators
+        x *= 1e18
+        w[4:60] *= 1e18
     elif kind == "zero_rows":
         x[5:9] = 0.0
         w[2] = 0.0
