@@ -49,14 +49,14 @@ struct SmallOperand<float> {
     bf16x8 h, m, l;
   };
   static __device__ __forceinline__ void set(Raw& r, int e, float v) { r.x[e] = v; }
-  static __device__ __forceinline__ Frag frag(const Raw& r) {
+  static __device__ __forceinline__ Frag frag(const Raw& r, float scale) {
     uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;  // (-1, 0), (0, -1): see DmaMma<float>::split
     __asm__("" : "+s"(c0), "+s"(c1));
     const bf16x2 n0 = __builtin_bit_cast(bf16x2, c0), n1 = __builtin_bit_cast(bf16x2, c1);
     u32x4 h, m, l;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const f32x2 v = {r.x[2 * e] * X6_SCALE, r.x[2 * e + 1] * X6_SCALE};
+      const f32x2 v = {r.x[2 * e] * scale, r.x[2 * e + 1] * scale};
       const bf16x2 hh = __builtin_convertvector(v, bf16x2);
       const f32x2 s = {__builtin_amdgcn_fdot2_f32_bf16(hh, n0, v[0], false),
                        __builtin_amdgcn_fdot2_f32_bf16(hh, n1, v[1], false)};
@@ -87,6 +87,7 @@ struct SmallOperand<float> {
     return ((r.x[0] + r.x[1]) + (r.x[2] + r.x[3])) + ((r.x[4] + r.x[5]) + (r.x[6] + r.x[7]));
   }
   static __device__ __forceinline__ float value(float v) { return v; }
+  static constexpr bool SIGNED = true;
   static constexpr float UNSCALE = X6_UNSCALE;  // of the accumulators
 };
 
@@ -100,13 +101,14 @@ struct SmallOperand<__bf16> {
     bf16x8 v;
   };
   static __device__ __forceinline__ void set(Raw& r, int e, unsigned short v) { r.x[e] = v; }
-  static __device__ __forceinline__ Frag frag(const Raw& r) { return {__builtin_bit_cast(bf16x8, r.x)}; }
+  static __device__ __forceinline__ Frag frag(const Raw& r, float) { return {__builtin_bit_cast(bf16x8, r.x)}; }
   template <int TN>
   static __device__ __forceinline__ void mfma(const Frag& a, const Frag (&b)[TN], f32x4 (&acc)[TN]) {
 #pragma unroll
     for (int q = 0; q < TN; ++q)
       acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[q].v, a.v, acc[q], 0, 0, 0);
   }
+  static constexpr bool SIGNED = false;
   static constexpr float UNSCALE = 1.f;
   static __device__ __forceinline__ float value(unsigned short v) { return __uint_as_float((uint32_t)v << 16); }
   static __device__ __forceinline__ float sum(const Raw& r) {
@@ -217,6 +219,8 @@ template <typename T, bool A_KC, bool B_KC, int TM, int TN, int WK, int DEPTH, b
 struct SmallGemm {
   static constexpr int BM = 16 * TM, BN = 16 * TN, NTHR = 64 * WK;
   static constexpr int PITCH = BN + 4;  // floats per LDS row of a partial tile
+  static constexpr int RUN = 8;  // K-steps an accumulator sums (256 terms)
+  static_assert(RUN % DEPTH == 0, "runs of whole rounds of loads");
   static constexpr int LDS_FLOATS = WK * BM * PITCH + WK * BM;
   using Op = SmallOperand<T>;
   using E = typename Op::Elem;
@@ -281,7 +285,41 @@ struct SmallGemm {
     float cs[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) cs[i] = 0.f;
+    // fp32: every other wave's share is summed negated (see DmaMma<float>)
+    const bool negated = Op::SIGNED && (wave & 1);
+    const float b_scale = negated ? -X6_SCALE : X6_SCALE;
     const bool cs_on = !A_KC && p.colsum != nullptr && n0 == 0;
+    // the wave's partial tile in LDS: stored, or added to what it has deposited
+    // before (every element is one lane's alone)
+    float* const part = lds + wave * BM * PITCH;
+    const float unscale = negated ? -Op::UNSCALE : Op::UNSCALE;
+    auto deposit = [&](bool add) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        float* row = part + (A_KC ? 16 * i + r16 : TM * r16 + i) * PITCH;
+#pragma unroll
+        for (int q = 0; q < TN; ++q) acc[i][q] *= unscale;
+        if constexpr (B_KC || TN == 1) {
+#pragma unroll
+          for (int q = 0; q < TN; ++q) {
+            f32x4* at = (f32x4*)&row[16 * q + 4 * g];
+            *at = add ? *at + acc[i][q] : acc[i][q];
+          }
+        } else {
+          // tile q's column r is column TN r + q
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            typedef float f32xTN __attribute__((ext_vector_type(TN)));
+            f32xTN v;
+#pragma unroll
+            for (int q = 0; q < TN; ++q) v[q] = acc[i][q][e];
+            f32xTN* at = (f32xTN*)&row[TN * (4 * g + e)];
+            *at = add ? *at + v : v;
+          }
+        }
+      }
+    };
+    bool deposited = false;
     auto multiply = [&](const typename Op::Raw (&xa)[TM], const typename Op::Raw (&xb)[TN]) {
       if constexpr (!A_KC) {
         if (cs_on) {
@@ -291,10 +329,10 @@ struct SmallGemm {
       }
       typename Op::Frag fb[TN];
 #pragma unroll
-      for (int q = 0; q < TN; ++q) fb[q] = Op::frag(xb[q]);
+      for (int q = 0; q < TN; ++q) fb[q] = Op::frag(xb[q], b_scale);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const typename Op::Frag fa = Op::frag(xa[i]);
+        const typename Op::Frag fa = Op::frag(xa[i], X6_SCALE);
         Op::mfma(fa, fb, acc[i]);
       }
     };
@@ -354,6 +392,18 @@ struct SmallGemm {
         for (int u = 0; u < DEPTH; ++u) load_next(u);
 #pragma unroll 1
         for (int s = 0; s < n; s += DEPTH) {
+          // a long share is summed in runs of RUN K-steps, so that an
+          // accumulator takes no more roundings than those of a contraction
+          // split over the grid (fp32, K = 8144 in 8 shares: 4.9e-7 off 64
+          // bits, in runs 2.4e-7; 1% of the time at 16 steps a share)
+          if (s > 0 && s % RUN == 0) {
+            deposit(deposited);
+            deposited = true;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int q = 0; q < TN; ++q) acc[i][q] = f32x4{};
+          }
 #pragma unroll
           for (int u = 0; u < DEPTH; ++u) {
             if (u == 0 || s + u < n) multiply(xa[u], xb[u]);
@@ -378,26 +428,9 @@ struct SmallGemm {
       }
     }
 
+    deposit(deposited);
+
     // ---- the waves' partial tiles meet in LDS
-    float* const part = lds + wave * BM * PITCH;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int q = 0; q < TN; ++q) acc[i][q] *= Op::UNSCALE;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      float* row = part + (A_KC ? 16 * i + r16 : TM * r16 + i) * PITCH;
-      if constexpr (B_KC || TN == 1) {
-#pragma unroll
-        for (int q = 0; q < TN; ++q) *(f32x4*)&row[16 * q + 4 * g] = acc[i][q];
-      } else {
-        // tile q's column r is column TN r + q
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int q = 0; q < TN; ++q) row[TN * (4 * g + e) + q] = acc[i][q][e];
-      }
-    }
     float* const cs_part = lds + WK * BM * PITCH;
     if constexpr (!A_KC) {
       if (cs_on) {

@@ -184,3 +184,32 @@ def test_no_further_from_exact_than_fp32_sums(K, runs):
     want = dy.double().t() @ x.double()
     rel = float((dw.double() - want).norm() / want.norm())
     assert rel <= {64: 1.4e-7, 4096: 1.15e-6, 100352: 1.08e-6}[K], rel
+
+
+# one call's relative error against 64 bits, no larger than with fp32
+# instructions (bf16: than in sixteen runs of 256 terms): runs of an NT, an NN
+# and a TN product, and the shares of the small kernel's waves
+@pytest.mark.parametrize("what,M,N,K,bar", [
+    ("da", 509, 257, 383, 4.46e-7), ("db", 509, 257, 383, 4.71e-7), ("dx", 137, 3720, 1506, 2.86e-7),
+    ("dx", 24, 3264, 2643, 2.68e-7), ("dx", 833, 2808, 64, 2.50e-7), ("dx bf16", 300, 4096, 300, 1.153e-7),
+    ("dw bf16", 3320, 76, 752, 1.105e-7)])
+def test_no_further_from_exact_than_before_the_split(what, M, N, K, bar):
+    g = torch.Generator(DEV).manual_seed(1)
+    if what in ("da", "db"):  # gradients of a broadcast batch: M x N (contracted in b) x K columns
+        P, Q = 16, 8
+        a, w = (2 * torch.rand(s, generator=g, device=DEV) - 1 for s in ((P, 1, M, N), (1, Q, N, K)))
+        dc = torch.randn(P, Q, M, K, generator=g, device=DEV)
+        x, y = (dc, w.transpose(-1, -2)) if what == "da" else (a.transpose(-1, -2), dc)
+        out = torch.empty_like(a if what == "da" else w)
+        ws = torch.empty(max(1, b.matmul_workspace(x, y, out, reduce_into=True)), dtype=torch.uint8, device=DEV)
+        b.matmul(x, y, out, reduce_into=True, workspace=ws)
+        want = torch.matmul(x.double(), y.double().contiguous()).sum(1 if what == "da" else 0, keepdim=True)
+    else:
+        dt = torch.bfloat16 if "bf16" in what else torch.float32
+        x, w, dy = (torch.randn(s, generator=g, device=DEV).to(dt) for s in ((M, K), (N, K), (M, N)))
+        dx, dw = (torch.empty(M, K, device=DEV), None) if "dx" in what else (None, torch.empty(N, K, device=DEV))
+        ws = torch.empty(max(1, b.linear_bwd_workspace(x, w, dy, dx, dw)), dtype=torch.uint8, device=DEV)
+        b.linear_bwd(x, w, dy, dx, dw, workspace=ws)
+        out, want = (dx, dy.double() @ w.double()) if "dx" in what else (dw, dy.double().t() @ x.double())
+    rel = float((out.double() - want).norm() / want.norm())
+    assert rel <= bar, rel
