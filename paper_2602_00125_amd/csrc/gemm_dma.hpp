@@ -387,7 +387,7 @@ struct DmaMma;
 // from 2^104 on, an infinity or a NaN has parts that are infinite or NaN, and
 // sums from 2^80 on may overflow, so the accumulators are not finite. The
 // block checks that, and computes such a tile again with the fp32
-// instructions (plain_tile).
+// instructions.
 // (One multiplication a value. A check by row, which cannot see small values
 // beside large ones, was a quarter of an instruction: 8192^3 step 15.57 ms,
 // with the scale 16.09.)
@@ -502,6 +502,16 @@ struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
     step(&Planes::h, &Planes::m);
     step(&Planes::h, &Planes::h);
   }
+  // the k-step by the fp32 instructions
+  static __device__ __forceinline__ void plain(const Frags& f, f32x16 (&acc)[TM][TN]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int q = 0; q < TN; ++q)
+          acc[i][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.b[q][e], f.a[i][e], acc[i][q], 0, 0, 0);
+  }
   // column sums of an M-contiguous A over the k-step: tile i's value goes to
   // the lane's column (a_col)
   static __device__ __forceinline__ void colsum(const Frags& f, float (&cs)[TM]) {
@@ -522,13 +532,6 @@ struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
       }
     const float t = (z[0] + z[1]) + (z[2] + z[3]);
     return t != t;
-  }
-  // the sums the accumulators stand for
-  static __device__ __forceinline__ void unscale(f32x16 (&acc)[TM][TN], float by) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int q = 0; q < TN; ++q) acc[i][q] *= by;
   }
 };
 

@@ -252,12 +252,12 @@ template <> struct LdsElem<__bf16> { using type = unsigned short; };
 // Epilogue of the dense layer followed by a nonlinearity (Sec. 3.3 Eq. (5),
 // "Nonlinearities"): z = acc + b[n] is stored when p.z is set and act(z) goes
 // to C. No batch, split or accumulation (the host guarantees it). The lane
-// holds C[m0l + 32 i][n0l + 32 q + 8 g + 0..3] in acc[i][q][4g .. 4g+3]. One
+// holds C[m0l + 32 i][n0l + 32 q + 8 g + 0..3] / scale in acc[i][q][4g .. 4g+3]. One
 // copy per nonlinearity: the switch is taken once per block, outside the
 // unrolled stores.
 template <int ACT, int TM, int TN, bool VEC_C>
 __device__ __forceinline__ void act_store(const GemmParams& p, const f32x16 (&acc)[TM][TN],
-                                          int64_t m0l, int64_t n0l) {
+                                          int64_t m0l, int64_t n0l, float scale) {
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int64_t m = m0l + i * 32;
@@ -271,6 +271,7 @@ __device__ __forceinline__ void act_store(const GemmParams& p, const f32x16 (&ac
         const int64_t n = n0l + q * 32 + 8 * g;
         f32x4 v = {acc[i][q][4 * g + 0], acc[i][q][4 * g + 1], acc[i][q][4 * g + 2],
                    acc[i][q][4 * g + 3]};
+        v *= scale;
         if (VEC_C) {
           if (n >= p.N) continue;
           if (p.bias) v += *(const f32x4*)&p.bias[n];
@@ -295,13 +296,13 @@ __device__ __forceinline__ void act_store(const GemmParams& p, const f32x16 (&ac
 
 template <int TM, int TN, bool VEC_C>
 __device__ __forceinline__ void act_epilogue(const GemmParams& p, const f32x16 (&acc)[TM][TN],
-                                             int64_t m0l, int64_t n0l) {
+                                             int64_t m0l, int64_t n0l, float scale = 1.f) {
   switch (p.act) {
-    case kActRelu: act_store<kActRelu, TM, TN, VEC_C>(p, acc, m0l, n0l); break;
-    case kActSigmoid: act_store<kActSigmoid, TM, TN, VEC_C>(p, acc, m0l, n0l); break;
-    case kActTanh: act_store<kActTanh, TM, TN, VEC_C>(p, acc, m0l, n0l); break;
-    case kActGelu: act_store<kActGelu, TM, TN, VEC_C>(p, acc, m0l, n0l); break;
-    default: act_store<kActNone, TM, TN, VEC_C>(p, acc, m0l, n0l); break;
+    case kActRelu: act_store<kActRelu, TM, TN, VEC_C>(p, acc, m0l, n0l, scale); break;
+    case kActSigmoid: act_store<kActSigmoid, TM, TN, VEC_C>(p, acc, m0l, n0l, scale); break;
+    case kActTanh: act_store<kActTanh, TM, TN, VEC_C>(p, acc, m0l, n0l, scale); break;
+    case kActGelu: act_store<kActGelu, TM, TN, VEC_C>(p, acc, m0l, n0l, scale); break;
+    default: act_store<kActNone, TM, TN, VEC_C>(p, acc, m0l, n0l, scale); break;
   }
 }
 

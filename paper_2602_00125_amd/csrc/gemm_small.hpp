@@ -10,8 +10,8 @@
 // meet in LDS at the end, where they are added in wave order on the way to C.
 // Loads need no alignment beyond the element's and no padded copies: rows past
 // the matrix are read from the last row (their results are dropped), the K
-// tail element by element. What the split of fp32 values does not serve is
-// found per result and computed again by fp32 multiply-adds.
+// tail element by element. A wave whose sums are not finite (what the split
+// of fp32 values does not serve) takes its share again by the fp32 instructions.
 //
 // v_mfma_f32_16x16x32_bf16: lane l of the first (second) operand holds row
 // (column) l & 15, k group g = l >> 4. A K-step is 32 k, dealt to the groups by
@@ -83,11 +83,18 @@ struct SmallOperand<float> {
     step(&Frag::h, &Frag::m);
     step(&Frag::h, &Frag::h);
   }
+  // by the fp32 instructions: element e of every group is one k of four
+  template <int TN>
+  static __device__ __forceinline__ void plain(const Raw& a, const Raw (&b)[TN], f32x4 (&acc)[TN]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int q = 0; q < TN; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q].x[e], a.x[e], acc[q], 0, 0, 0);
+  }
   static __device__ __forceinline__ float sum(const Raw& r) {
     return ((r.x[0] + r.x[1]) + (r.x[2] + r.x[3])) + ((r.x[4] + r.x[5]) + (r.x[6] + r.x[7]));
   }
-  static __device__ __forceinline__ float value(float v) { return v; }
-  static constexpr bool SIGNED = true;
+  static constexpr bool SPLIT = true;
   static constexpr float UNSCALE = X6_UNSCALE;  // of the accumulators
 };
 
@@ -108,7 +115,7 @@ struct SmallOperand<__bf16> {
     for (int q = 0; q < TN; ++q)
       acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[q].v, a.v, acc[q], 0, 0, 0);
   }
-  static constexpr bool SIGNED = false;
+  static constexpr bool SPLIT = false;
   static constexpr float UNSCALE = 1.f;
   static __device__ __forceinline__ float value(unsigned short v) { return __uint_as_float((uint32_t)v << 16); }
   static __device__ __forceinline__ float sum(const Raw& r) {
@@ -278,22 +285,17 @@ struct SmallGemm {
       }
     };
     f32x4 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int q = 0; q < TN; ++q) acc[i][q] = f32x4{};
     float cs[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) cs[i] = 0.f;
     // fp32: every other wave's share is summed negated (see DmaMma<float>)
-    const bool negated = Op::SIGNED && (wave & 1);
+    const bool negated = Op::SPLIT && (wave & 1);
     const float b_scale = negated ? -X6_SCALE : X6_SCALE;
     const bool cs_on = !A_KC && p.colsum != nullptr && n0 == 0;
     // the wave's partial tile in LDS: stored, or added to what it has deposited
     // before (every element is one lane's alone)
     float* const part = lds + wave * BM * PITCH;
-    const float unscale = negated ? -Op::UNSCALE : Op::UNSCALE;
-    auto deposit = [&](bool add) {
+    auto deposit = [&](bool add, float unscale) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         float* row = part + (A_KC ? 16 * i + r16 : TM * r16 + i) * PITCH;
@@ -319,21 +321,41 @@ struct SmallGemm {
         }
       }
     };
-    bool deposited = false;
-    auto multiply = [&](const typename Op::Raw (&xa)[TM], const typename Op::Raw (&xb)[TN]) {
-      if constexpr (!A_KC) {
-        if (cs_on) {
+    auto clear = [&]() {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) cs[i] += Op::sum(xa[i]);
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int q = 0; q < TN; ++q) acc[i][q] = f32x4{};
+    };
+    auto not_finite = [&]() {
+      float z = 0.f;  // 0 x finite = 0, 0 x (inf or NaN) = NaN
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int q = 0; q < TN; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) z = __builtin_fmaf(acc[i][q][e], 0.f, z);
+      return z != z;
+    };
+    auto multiply = [&](auto plain, const typename Op::Raw (&xa)[TM], const typename Op::Raw (&xb)[TN]) {
+      if constexpr (decltype(plain)::value) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) std::conditional_t<decltype(plain)::value, Op, void>::plain(xa[i], xb, acc[i]);
+      } else {
+        if constexpr (!A_KC) {
+          if (cs_on) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) cs[i] += Op::sum(xa[i]);
+          }
         }
-      }
-      typename Op::Frag fb[TN];
+        typename Op::Frag fb[TN];
 #pragma unroll
-      for (int q = 0; q < TN; ++q) fb[q] = Op::frag(xb[q], b_scale);
+        for (int q = 0; q < TN; ++q) fb[q] = Op::frag(xb[q], b_scale);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const typename Op::Frag fa = Op::frag(xa[i], X6_SCALE);
-        Op::mfma(fa, fb, acc[i]);
+        for (int i = 0; i < TM; ++i) {
+          const typename Op::Frag fa = Op::frag(xa[i], X6_SCALE);
+          Op::mfma(fa, fb, acc[i]);
+        }
       }
     };
     // The K-steps of every summed batch element: KF that load() takes, then
@@ -356,7 +378,11 @@ struct SmallGemm {
       }
       return {b0 + (uint32_t)((uint64_t)n * w / WK), b0 + (uint32_t)((uint64_t)n * (w + 1) / WK)};
     };
-    {
+    // The wave's share, deposited; whether a sum of it is not finite.
+    auto take_share = [&](auto plain) {
+      const float unscale = decltype(plain)::value ? 1.f : negated ? -Op::UNSCALE : Op::UNSCALE;
+      bool bad = false, deposited = false;
+      clear();
       const Share f = share(KF * R, wave);
       const int n = (int)(f.hi - f.lo);
       uint32_t cr = 0, ck = f.lo;  // the next K-step to load
@@ -372,7 +398,6 @@ struct SmallGemm {
         pa = la.base + ra + ck * da;
         pb = lb.base + rb + ck * db;
       };
-      if (n > 0) seek();
       typename Op::Raw xa[DEPTH][TM], xb[DEPTH][TN];
       int left = n;  // steps not yet loaded
       auto load_next = [&](int u) {
@@ -388,6 +413,7 @@ struct SmallGemm {
         }
       };
       if (n > 0) {
+        seek();
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) load_next(u);
 #pragma unroll 1
@@ -397,38 +423,43 @@ struct SmallGemm {
           // split over the grid (fp32, K = 8144 in 8 shares: 4.9e-7 off 64
           // bits, in runs 2.4e-7; 1% of the time at 16 steps a share)
           if (s > 0 && s % RUN == 0) {
-            deposit(deposited);
+            bad |= Op::SPLIT && not_finite();
+            deposit(deposited, unscale);
             deposited = true;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-              for (int q = 0; q < TN; ++q) acc[i][q] = f32x4{};
+            clear();
           }
 #pragma unroll
           for (int u = 0; u < DEPTH; ++u) {
-            if (u == 0 || s + u < n) multiply(xa[u], xb[u]);
+            if (u == 0 || s + u < n) multiply(plain, xa[u], xb[u]);
             load_next(u);
           }
         }
       }
-    }
-    if (KF < KS) {
-      typename Op::Raw xa[TM], xb[TN];
-      const Share e = share(R, wave);
+      if (KF < KS) {
+        const Share e = share(R, wave);
 #pragma unroll 1
-      for (uint32_t r = e.lo; r < e.hi; ++r) {
-        int64_t ra, rb;
-        red_off(r, ra, rb);
+        for (uint32_t r = e.lo; r < e.hi; ++r) {
+          int64_t ra, rb;
+          red_off(r, ra, rb);
 #pragma unroll 1
-        for (uint32_t st = KF; st < KS; ++st) {
-          la.load_edge(xa, ra, (int64_t)st * 32, p.K, lane);
-          lb.load_edge(xb, rb, (int64_t)st * 32, p.K, lane);
-          multiply(xa, xb);
+          for (uint32_t st = KF; st < KS; ++st) {
+            la.load_edge(xa[0], ra, (int64_t)st * 32, p.K, lane);
+            lb.load_edge(xb[0], rb, (int64_t)st * 32, p.K, lane);
+            multiply(plain, xa[0], xb[0]);
+          }
         }
       }
+      bad |= Op::SPLIT && not_finite();
+      deposit(deposited, unscale);
+      return bad;
+    };
+    const bool bad = take_share(std::false_type{});
+    if constexpr (Op::SPLIT) {
+      // what the split does not serve: the share again, by the fp32
+      // instructions (16 x 4096 x 4096 forward 23.4 us, with one NaN in x
+      // 24.7, all NaN 37; a thread for each result instead: 1.5 ms)
+      if (__any(bad)) take_share(std::true_type{});
     }
-
-    deposit(deposited);
 
     // ---- the waves' partial tiles meet in LDS
     float* const cs_part = lds + WK * BM * PITCH;
@@ -469,38 +500,6 @@ struct SmallGemm {
       f32x4 v = *(const f32x4*)&lds[mr * PITCH + nr];
 #pragma unroll
       for (int w = 1; w < WK; ++w) v += *(const f32x4*)&lds[(w * BM + mr) * PITCH + nr];
-      if constexpr (std::is_same_v<T, float>) {
-        uint32_t again = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (v[e] * 0.f != 0.f) again |= 1u << e;
-        if (again) {
-          // fp32 multiply-adds from memory for what the split does not serve (rare)
-#pragma unroll 1
-          for (int e = 0; e < 4; ++e) {
-            if (!((again >> e) & 1u) || n + e >= p.N) continue;
-            float s = 0.f;
-#pragma unroll 1
-            for (uint32_t w = 0; w < WK; ++w) {
-              auto terms = [&](uint32_t r, int64_t k0, int64_t k1) {
-                int64_t xr, yr;
-                red_off(r, xr, yr);
-                const E* a = (const E*)p.a + a_off + xr + (A_KC ? m * p.lda : m);
-                const E* b = (const E*)p.b + b_off + yr + (B_KC ? (n + e) * p.ldb : n + e);
-#pragma unroll 1
-                for (int64_t k = k0; k < k1 && k < p.K; ++k)
-                  s = __builtin_fmaf(Op::value(a[A_KC ? k : k * p.lda]), Op::value(b[B_KC ? k : k * p.ldb]), s);
-              };
-              const Share f = share(KF * R, w), g2 = share(R, w);
-              for (uint32_t i = f.lo; i < f.hi; ++i) terms(i / KF, (int64_t)(i % KF) * 32, (int64_t)(i % KF) * 32 + 32);
-              if (KF < KS)
-                for (uint32_t r = g2.lo; r < g2.hi; ++r) terms(r, (int64_t)KF * 32, (int64_t)KS * 32);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = i == e ? s : v[i];
-          }
-        }
-      }
       float* c = C + m * ldc + n;
       float* z = p.z ? p.z + m * p.ldz + n : nullptr;
       const int cnt = p.N - n < 4 ? (int)(p.N - n) : 4;
