@@ -140,12 +140,11 @@ def test_convolution_of_values_the_split_does_not_serve(kind, stride):
         return out.detach(), ga, gk
 
     try:
-        for sk in (0, 2):
+        for sk in (0, 1, 2):  # 1: as chosen, the phases in one grid of 128x128 tiles
             b.debug_set("stream_k", sk)
-            b.debug_set("sk_blocks", 5 if sk else 0)
+            b.debug_set("sk_blocks", 5 if sk == 2 else 0)
             b.debug_set("phase_grid", sk)
-            if sk:
-                b.debug_set("cfg", 6)
+            b.debug_set("cfg", 6 if sk == 2 else -1)
             k1 = max(b.conv2d_fwd_workspace(xd, wd, None, y, stride, 1),
                      b.conv2d_bwd_workspace(xd, wd, dyd, dx, dw, db, stride, 1))
             ws = torch.empty(max(1, k1), dtype=torch.uint8, device=DEV)
@@ -213,3 +212,59 @@ def test_no_further_from_exact_than_before_the_split(what, M, N, K, bar):
         out, want = (dx, dy.double() @ w.double()) if "dx" in what else (dw, dy.double().t() @ x.double())
     rel = float((out.double() - want).norm() / want.norm())
     assert rel <= bar, rel
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan", "big_sums"])
+@pytest.mark.parametrize("cfg,vec1", [(6, 0), (10, 0), (10, 1), (8, 1), (16, 0), (17, 0), (18, 0)])
+def test_refused_values_through_every_epilogue(cfg, vec1, kind):
+    """The pass by the fp32 instructions ends in the same epilogues: a
+    nonlinearity with z, adding to the outputs, both gradients and db in one
+    launch, kept and summed batch elements, runs. (K with and without a tail.)"""
+    g = torch.Generator().manual_seed(cfg)
+    M, N = 300, 200
+    try:
+        b.debug_set("cfg", cfg)
+        b.debug_set("vec1", vec1)
+        for K in (128, 77):
+            x, w = spoil(torch.randn(M, K, generator=g), torch.randn(N, K, generator=g), kind)
+            X, W = x.double(), w.double()
+            want, S = X @ W.t(), X.abs() @ W.t().abs()
+            bias = torch.randn(N, generator=g)
+            z, h = (torch.full((M, N), math.nan, device=DEV) for _ in range(2))
+            b.linear_act_fwd(x.to(DEV), w.to(DEV), bias.to(DEV), "gelu", h, z)
+            check(z, want + bias.double(), S + bias.double().abs(), K, "z")
+            fin = torch.isfinite(z)
+            near = torch.nn.functional.gelu(z.double())
+            assert bool(((h.double() - near).abs() <= 1e-5 * z.double().abs() + 1e-6)[fin].all())
+            # dY = x [M x K], W = w^T [K x N], X = the same rows again
+            dy, wt = x.to(DEV), w.t().contiguous().to(DEV)
+            xs = torch.randn(M, N, generator=g)
+            prior = torch.randn(M, N, generator=g), torch.randn(K, N, generator=g), torch.randn(K, generator=g)
+            wdw, Sdw = X.t() @ xs.double(), X.t().abs() @ xs.double().abs()
+            for splits in (0, 3):
+                b.debug_set("splits", splits)  # 0: a small cfg takes both gradients in one launch
+                for acc in (False, True):
+                    dx, dw, db = ((p if acc else torch.full_like(p, math.nan)).to(DEV) for p in prior)
+                    ws = torch.empty(max(1, b.linear_bwd_workspace(xs.to(DEV), wt, dy, dx, dw, db)), dtype=torch.uint8,
+                                     device=DEV)
+                    b.linear_bwd(xs.to(DEV), wt, dy, dx, dw, db, accumulate=acc, workspace=ws)
+                    for got, v, s, p, n in ((dx, want, S, prior[0], K), (dw, wdw, Sdw, prior[1], M),
+                                            (db, X.sum(0), X.abs().sum(0), prior[2], M)):
+                        p = p.double() * acc
+                        check(got, v + p, s + p.abs(), n, f"{splits} {acc}")
+                # a batch of two kept and three summed elements
+                A = torch.stack([torch.stack([x, x * 0.5, -x]) for _ in range(2)])
+                B = torch.stack([torch.stack([w, w, w * 2]) for _ in range(2)])
+                for red in (False, True):
+                    c = torch.full((2, 1 if red else 3, M, N), math.nan, device=DEV)
+                    At, Bt = A.to(DEV), B.to(DEV).transpose(-1, -2)
+                    ws = torch.empty(max(1, b.matmul_workspace(At, Bt, c, reduce_into=red)), dtype=torch.uint8, device=DEV)
+                    b.matmul(At, Bt, c, reduce_into=red, workspace=ws)
+                    wc, Sc = A.double() @ B.double().transpose(-1, -2), A.double().abs() @ B.double().abs().transpose(-1, -2)
+                    if red:
+                        wc, Sc = wc.sum(1, keepdim=True), Sc.sum(1, keepdim=True)
+                    check(c, wc, Sc, 3 * K if red else K, f"batch {red} {splits}")
+            b.debug_set("splits", 0)
+    finally:
+        for k, v in (("cfg", -1), ("vec1", 0), ("splits", 0)):
+            b.debug_set(k, v)
