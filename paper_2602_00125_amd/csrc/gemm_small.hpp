@@ -168,11 +168,14 @@ struct SmallLoader {
     }
   }
   // K-steps from the first that load() may take: whole ones, and on an edge
-  // tile of an M/N-contiguous operand not the one with the last row of all
-  // (none where rows are shorter than a vector)
+  // tile of an M/N-contiguous operand none of the last rows from which a
+  // vector would run past the matrix's last element (the last row; several of
+  // rows shorter than a vector; all where rows coincide)
   __device__ __forceinline__ int64_t whole_steps(int64_t K) const {
-    if (KC || left >= 16 * NT) return K / 32;
-    return ld >= NT ? (K - 1) / 32 : 0;
+    if (KC || NT == 1 || left >= 16 * NT) return K / 32;
+    if (ld <= 0) return 0;
+    const int64_t rows = K - (ld >= NT ? 1 : (NT - 1 + ld - 1) / ld);
+    return rows > 0 ? rows / 32 : 0;
   }
   // p: base + batch offset + the K-step's origin
   __device__ __forceinline__ void load(typename Op::Raw (&x)[NT], const E* p) const {
@@ -359,8 +362,9 @@ struct SmallGemm {
       }
     };
     // The K-steps of every summed batch element: KF that load() takes, then
-    // the rest (at most one) element by element. This wave takes its share
-    // of the first and of the second (32-bit: the host bounds their number).
+    // the rest (one or two, all of them where rows coincide) element by
+    // element. This wave takes its share of the first and of the second
+    // (32-bit: the host bounds their number).
     const uint32_t KS = (uint32_t)((p.K + 31) / 32);
     uint32_t KF = 0;
     if (p.K > 0) {
@@ -436,17 +440,16 @@ struct SmallGemm {
         }
       }
       if (KF < KS) {
-        const Share e = share(R, wave);
+        const uint32_t edges = KS - KF;
+        const Share e = share(edges * R, wave);
 #pragma unroll 1
-        for (uint32_t r = e.lo; r < e.hi; ++r) {
+        for (uint32_t i = e.lo; i < e.hi; ++i) {
+          const uint32_t r = i / edges, st = KF + (i - r * edges);
           int64_t ra, rb;
           red_off(r, ra, rb);
-#pragma unroll 1
-          for (uint32_t st = KF; st < KS; ++st) {
-            la.load_edge(xa[0], ra, (int64_t)st * 32, p.K, lane);
-            lb.load_edge(xb[0], rb, (int64_t)st * 32, p.K, lane);
-            multiply(plain, xa[0], xb[0]);
-          }
+          la.load_edge(xa[0], ra, (int64_t)st * 32, p.K, lane);
+          lb.load_edge(xb[0], rb, (int64_t)st * 32, p.K, lane);
+          multiply(plain, xa[0], xb[0]);
         }
       }
       bad |= Op::SPLIT && not_finite();

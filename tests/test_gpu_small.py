@@ -122,6 +122,56 @@ def test_values_the_split_does_not_serve(cfg, kind):
         b.debug_set("cfg", -1)
 
 
+def best_time(f):
+    f()
+    best = math.inf
+    for _ in range(5):
+        a, e = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(4):
+            f()
+        e.record()
+        e.synchronize()
+        best = min(best, a.elapsed_time(e))
+    return best
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 5])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_layers_of_a_few_outputs(N, dtype):
+    """dW of a head of N outputs: rows of dY shorter than the tile's vectors,
+    up to the matrix's last element (what follows is NaN) and no further, at
+    remainders around a K-step; and its contraction is shared by the waves."""
+    g = torch.Generator().manual_seed(N)
+    K = 70
+    try:
+        for cfg in (16, 17, 18):
+            b.debug_set("cfg", cfg)
+            for M in (1, 2, 31, 32, 33, 34, 35, 64, 67, 97, 330):
+                x, dy, w = (torch.randn(s, generator=g).to(dtype) for s in ((M, K), (M, N), (N, K)))
+                buf = torch.full((M * N + 8,), math.nan, dtype=dtype, device=DEV)
+                d = buf[:M * N].view(M, N)
+                d.copy_(dy)
+                X, D, W = x.double(), dy.double(), w.double()
+                dx, dw, db = (torch.full(s, math.nan, device=DEV) for s in ((M, K), (N, K), (N,)))
+                b.linear_bwd(x.to(DEV), w.to(DEV), d, dx, dw, db)
+                close(dw, D.t() @ X, D.t().abs() @ X.abs(), M, f"dw {cfg} {M}")
+                close(dx, D @ W, D.abs() @ W.abs(), N, f"dx {cfg} {M}")
+                close(db, D.sum(0), D.abs().sum(0), M, f"db {cfg} {M}")
+    finally:
+        b.debug_set("cfg", -1)
+    M, K = 8192, 1024
+
+    def step(n):
+        x, dy, w = (torch.randn(s, device=DEV).to(dtype) for s in ((M, K), (M, n), (n, K)))
+        o = torch.empty(M, K, device=DEV), torch.empty(n, K, device=DEV), torch.empty(n, device=DEV)
+        ws = torch.empty(max(1, b.linear_bwd_workspace(x, w, dy, *o)), dtype=torch.uint8, device=DEV)
+        return best_time(lambda: b.linear_bwd(x, w, dy, *o, workspace=ws))
+
+    # one wave walking 256 K-steps alone took 7 times as long as 64 outputs
+    assert step(N) < 3 * step(64)
+
+
 def test_runs_of_a_long_contraction():
     """A 16x16 weight gradient over 20000 rows: split over the grid when a
     workspace is given, whole without one; db in the same launch."""
