@@ -239,74 +239,67 @@ FN(conv2d_bwd) {  // x, w, dy, dx, dw, db, sh, sw, ph, pw, flags, ws, stream
   return call(g.ok, [&] { return L.conv2d_bwd(x, w, dy, dx, dw, db, v[0], v[1], v[2], v[3], flags, ws.p, ws.n, st); });
 }
 
-// Descriptors of `lists` sequences of n tensors each, one array after another.
-mt_tensor* arrays(PyObject* const* a, int lists, Py_ssize_t* n) {
-  mt_tensor* out = nullptr;
+// Descriptors of up to four lists of n tensors each, one list after another.
+// The lists' tensors are held until the call has returned: it runs without
+// the interpreter's lock, while another thread may change a list, and an
+// iterable may make its tensors as it is read. What has no length is refused.
+struct Lists {
+  PyObject* held[4] = {};
+  mt_tensor* d = nullptr;
+  Py_ssize_t n = 0;
   bool ok = true;
-  for (int l = 0; ok && l < lists; ++l) {
-    PyObject* seq = PySequence_Fast(a[l], "expected a sequence of tensors");
-    if (!seq) {
-      ok = false;
-      break;
-    }
-    const Py_ssize_t k = PySequence_Fast_GET_SIZE(seq);
-    if (l == 0) {
-      *n = k;
-      out = (mt_tensor*)PyMem_Malloc(sizeof(mt_tensor) * (size_t)(lists * (k > 0 ? k : 1)));
-      if (!out) {
-        PyErr_NoMemory();
-        ok = false;
-      }
-    } else if (k != *n) {
+  Lists(PyObject* const* a, int lists) {
+    for (int l = 0; ok && l < lists; ++l) ok = PyObject_Size(a[l]) >= 0 && (held[l] = PySequence_Tuple(a[l])) != nullptr;
+    if (!ok) return;
+    n = PyTuple_GET_SIZE(held[0]);
+    for (int l = 1; l < lists; ++l) {
+      if (PyTuple_GET_SIZE(held[l]) == n) continue;
       PyErr_SetString(PyExc_AssertionError, "the lists of tensors have different lengths");
       ok = false;
+      return;
     }
-    for (Py_ssize_t i = 0; ok && i < k; ++i) ok = describe(PySequence_Fast_GET_ITEM(seq, i), &out[l * k + i]);
-    Py_DECREF(seq);
+    d = (mt_tensor*)PyMem_Malloc(sizeof(mt_tensor) * (size_t)(lists * (n > 0 ? n : 1)));
+    if (!d) {
+      PyErr_NoMemory();
+      ok = false;
+    }
+    for (int l = 0; ok && l < lists; ++l)
+      for (Py_ssize_t i = 0; ok && i < n; ++i) ok = describe(PyTuple_GET_ITEM(held[l], i), &d[l * n + i]);
   }
-  if (!ok) {
-    PyMem_Free(out);
-    return nullptr;
+  ~Lists() {
+    PyMem_Free(d);
+    for (PyObject* h : held) Py_XDECREF(h);
   }
-  return out;
-}
+  const mt_tensor* operator[](int l) const { return d + l * n; }
+};
 
 FN(sgd_step) {  // params, grads, velocity, lr, momentum, weight_decay, stream
   Args g(a, n, 7);
   if (!g.ok) return nullptr;
-  Py_ssize_t k = 0;
-  mt_tensor* t = arrays(a, 3, &k);
-  if (!t) return nullptr;
+  const Lists t(a, 3);
+  if (!t.ok) return nullptr;
   const float lr = g.f32(3), mu = g.f32(4), wd = g.f32(5);
   void* st = g.stream(6);
-  PyObject* r = call(g.ok, [&] { return L.sgd_step((int32_t)k, t, t + k, t + 2 * k, lr, mu, wd, st); });
-  PyMem_Free(t);
-  return r;
+  return call(g.ok, [&] { return L.sgd_step((int32_t)t.n, t[0], t[1], t[2], lr, mu, wd, st); });
 }
 FN(adam_step) {  // params, grads, exp_avg, exp_avg_sq, lr, beta1, beta2, eps, step, stream
   Args g(a, n, 10);
   if (!g.ok) return nullptr;
-  Py_ssize_t k = 0;
-  mt_tensor* t = arrays(a, 4, &k);
-  if (!t) return nullptr;
+  const Lists t(a, 4);
+  if (!t.ok) return nullptr;
   const float lr = g.f32(4), b1 = g.f32(5), b2 = g.f32(6), eps = g.f32(7);
   const int64_t step = g.i64(8);
   void* st = g.stream(9);
-  PyObject* r = call(g.ok, [&] { return L.adam_step((int32_t)k, t, t + k, t + 2 * k, t + 3 * k, lr, b1, b2, eps, step, st); });
-  PyMem_Free(t);
-  return r;
+  return call(g.ok, [&] { return L.adam_step((int32_t)t.n, t[0], t[1], t[2], t[3], lr, b1, b2, eps, step, st); });
 }
 FN(rmsprop_step) {  // params, grads, sq_avg, lr, alpha, eps, stream
   Args g(a, n, 7);
   if (!g.ok) return nullptr;
-  Py_ssize_t k = 0;
-  mt_tensor* t = arrays(a, 3, &k);
-  if (!t) return nullptr;
+  const Lists t(a, 3);
+  if (!t.ok) return nullptr;
   const float lr = g.f32(3), alpha = g.f32(4), eps = g.f32(5);
   void* st = g.stream(6);
-  PyObject* r = call(g.ok, [&] { return L.rmsprop_step((int32_t)k, t, t + k, t + 2 * k, lr, alpha, eps, st); });
-  PyMem_Free(t);
-  return r;
+  return call(g.ok, [&] { return L.rmsprop_step((int32_t)t.n, t[0], t[1], t[2], lr, alpha, eps, st); });
 }
 
 FN(init) {

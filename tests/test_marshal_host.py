@@ -30,3 +30,47 @@ def test_missing_descriptors_are_the_library_s_error():
     with pytest.raises(b.MtError) as e:
         b.linear_fwd(None, None, None, None, stream=0)
     assert e.value.name == "MT_ERR_NULL"
+
+
+class _Made:
+    """A tensor to the marshalling, with no memory behind it."""
+    is_cuda, dtype, shape = True, torch.float32, (4,)
+    live = 0
+
+    def __init__(self):
+        _Made.live += 1
+
+    def __del__(self):
+        _Made.live -= 1
+
+    def stride(self):
+        return (1,)
+
+    def data_ptr(self):
+        _Made.seen = max(_Made.seen, _Made.live)
+        return 4096 * _Made.live
+
+
+class _Makes:
+    """A list whose tensors are made as it is read."""
+
+    def __len__(self):
+        return 2
+
+    def __iter__(self):
+        return (_Made() for _ in range(2))
+
+
+def test_tensors_of_lists_are_held_until_the_call_returns():
+    _Made.seen = 0
+    with pytest.raises(b.MtError, match="step counts from 1"):  # refused before any memory is touched
+        b.adam_step(_Makes(), _Makes(), _Makes(), _Makes(), 0.1, 0.9, 0.999, 1e-8, 0, stream=0)
+    assert _Made.seen == 8 and _Made.live == 0
+
+
+@pytest.mark.parametrize("call", [
+    lambda t: b.sgd_step(t(), [], [], 0.1, stream=0), lambda t: b.adam_step([], t(), [], [], 0.1, 0.9, 0.999, 1e-8, 1, stream=0),
+    lambda t: b.rmsprop_step([], [], t(), 0.1, 0.9, 1e-8, stream=0)])
+def test_generators_are_refused(call):
+    with pytest.raises(TypeError):
+        call(lambda: (x for x in []))
