@@ -297,12 +297,16 @@ hipError_t launch_opt(OptBatch b, const Op& op, hipStream_t stream) {
 
 constexpr int kActBwdWaves = 16;
 
-// Row slices of the pullback with db: up to 512 blocks (two a CU), slices of
-// at least two rows a wave (512 x 1024: 2 slices on 8 blocks 13.8 us, 16 on
-// 64 blocks about 5).
+// Row slices of the pullback with db: 512 blocks (two a CU), slices of at
+// least two rows a wave (512 x 1024: 2 slices on 8 blocks 13.8 us, 16 on 64
+// blocks about 5). 256 blocks once whole rows of 16-byte accesses keep every
+// CU busy by themselves (8192^2: 156 us against 166, 16384 x 1024 37.3 against
+// 42; 4096 x 1024 17.6 against 14.5).
 int act_bwd_parts(int64_t M, int64_t N) {
-  const int64_t col_blocks = (N + 255) / 256;
-  int64_t parts = 512 / (col_blocks > 0 ? col_blocks : 1);
+  const bool vec = N % 4 == 0;
+  const int64_t cols = vec ? 256 : 64;  // of a block
+  const int64_t col_blocks = (N + cols - 1) / cols;
+  int64_t parts = (vec && M * N >= (int64_t)1 << 23 ? 256 : 512) / (col_blocks > 0 ? col_blocks : 1);
   if (parts > M / (2 * kActBwdWaves)) parts = M / (2 * kActBwdWaves);
   if (parts > 256) parts = 256;
   return parts < 1 ? 1 : (int)parts;

@@ -35,3 +35,20 @@ def _dw_workspace(cfg, M, N, K):
 @pytest.mark.parametrize("M", [64, 96, 1000])
 def test_fp32_tiles_are_planned_as_the_ring_tiles_they_run_on(cfg, ring, M):
     assert _dw_workspace(cfg, M, 512, 256) == _dw_workspace(ring, M, 512, 256) > 0
+
+
+def _workspace(fn, *args):
+    n = ctypes.c_size_t(0)
+    assert fn(*args, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("M,N,parts", [(512, 1024, 16), (4096, 1024, 128), (4000, 1001, 32), (300, 8191, 4),
+                                       (8192, 8192, 8), (16384, 1024, 64), (20, 64, 0)])
+def test_row_slices_of_the_activation_pullback(M, N, parts):
+    """About 512 blocks, counted in the columns a block takes (64 where rows
+    are odd); 256 where long rows fill every CU by themselves."""
+    g = 1 << 36
+    z, dy, dz, db = _t([M, N], g), _t([M, N], 2 * g), _t([M, N], 3 * g), _t([N], 4 * g)
+    r = ctypes.byref
+    assert _workspace(b.lib.mt_act_bwd_workspace, 4, r(z), r(dy), r(dz), r(db)) == 4 * parts * N
