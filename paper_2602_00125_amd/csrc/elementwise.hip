@@ -346,7 +346,10 @@ hipError_t act_bwd(int act, const float* z, int64_t ldz, const void* dh, int64_t
 }
 
 int mse_parts(int64_t n) {
-  // blocks of at least four 16-byte loads a lane from each operand
+  // one block while a second launch would cost more than its work shared out
+  // (12000: 5.5 us against 5.8; 16384: 6.5 against 5.7), then blocks of at
+  // least four 16-byte loads a lane from each operand
+  if (n <= 12288) return 1;
   int64_t parts = (n + 4095) / 4096;
   if (parts > 1024) parts = 1024;
   if (parts < 1) parts = 1;

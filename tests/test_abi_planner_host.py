@@ -43,6 +43,14 @@ def _workspace(fn, *args):
     return n.value
 
 
+@pytest.mark.parametrize("n,parts", [(1, 0), (5120, 0), (12288, 0), (12289, 4), (1 << 20, 256)])
+def test_a_small_mean_squared_error_is_one_launch(n, parts):
+    """(no parts: no second launch adds them)"""
+    g = 1 << 32
+    p, t = _t([n], g), _t([n], 2 * g)
+    assert _workspace(b.lib.mt_mse_loss_workspace, ctypes.byref(p), ctypes.byref(t)) == 4 * parts
+
+
 @pytest.mark.parametrize("M,N,parts", [(512, 1024, 16), (4096, 1024, 128), (4000, 1001, 32), (300, 8191, 4),
                                        (8192, 8192, 8), (16384, 1024, 64), (20, 64, 0)])
 def test_row_slices_of_the_activation_pullback(M, N, parts):
