@@ -445,8 +445,9 @@ static hipError_t reduce_launch(const float* x, const ReducePlan& plan, float* o
                      dim3((unsigned)((plan.keep_count + 256 / GG - 1) / (256 / GG)), (unsigned)parts), dim3(256), 0, \
                      stream, x, plan, out, (int)accumulate, ws, per4)
     // a group for each output; the block's 256 lanes once an output has four
-    // loads for each of them
-    if (lanes >= 1024) { if (vec) MT_REDUCE(4, 256); else MT_REDUCE(1, 256); }
+    // loads for each of them, below 2^24 outputs: a launch takes fewer than
+    // 2^32 threads (that many outputs fill the chip with a wave each)
+    if (lanes >= 1024 && plan.keep_count < (int64_t)1 << 24) { if (vec) MT_REDUCE(4, 256); else MT_REDUCE(1, 256); }
     else if (lanes > 32) { if (vec) MT_REDUCE(4, 64); else MT_REDUCE(1, 64); }
     else if (lanes > 8) { if (vec) MT_REDUCE(4, 16); else MT_REDUCE(1, 16); }
     else { if (vec) MT_REDUCE(4, 4); else MT_REDUCE(1, 4); }

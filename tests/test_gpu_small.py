@@ -226,6 +226,16 @@ def test_reduction(shape, keep, view):
             b.debug_set("parts", 0)
 
 
+@pytest.mark.parametrize("n", [(1 << 24) - 1, (1 << 24) + 3])
+def test_reduction_to_many_outputs_of_long_sums(n):
+    """A block an output would be a launch of 2^32 threads."""
+    row = torch.randn(4096, generator=torch.Generator().manual_seed(0))
+    out = torch.full((n, 1), math.nan, device=DEV)
+    b.reduce_broadcast_grad(row.to(DEV).expand(n, 4096), out)
+    assert bool((out == out[0]).all())
+    close(out[0], row.double().sum(), row.double().abs().sum(), 4096, "sum")
+
+
 from test_gpu_conv import PHASE_CASES, check as conv_check, make as conv_make, run as conv_run  # noqa: E402
 
 
