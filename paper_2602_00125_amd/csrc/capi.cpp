@@ -534,7 +534,7 @@ mt_status launch_gemm(GemmCall& g, hipStream_t stream, void* ws, size_t ws_bytes
   }
   // (the workspace queries go by the ring tiles' plan, whatever runs)
   double est;
-  if (mt::relu_saves_z(p)) {
+  if (mt::relu_layer(p)) {
     // one order of its sums: the tile that was asked for
   } else if (const int small = choose_small(g, &est); small >= 0) {
     g = asked;

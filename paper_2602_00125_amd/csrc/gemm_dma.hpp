@@ -536,7 +536,7 @@ struct DmaMma<float, A_KC, B_KC, TM, TN, BK, BM, BN> {
 };
 
 // fp32 products on the fp32 instructions, K-contiguous operands: the sums of a
-// ReLU layer that saves its pre-activation (see relu_saves_z). A k-step is a
+// ReLU layer (see relu_layer). A k-step is a
 // group of 8 k; within it, MFMA step j (0..3) takes k = 8g + 4h + j for lane
 // half h (one 16-byte read of a tile row feeds 4 steps).
 template <int TM, int TN, int BK, int BM, int BN>

@@ -117,9 +117,9 @@ static hipError_t launch_epi(const GemmParams& p, bool vec, int cfg, hipStream_t
   return launch_dma<true, true, 128, 128, 32, 2, 2, 2, 2, true>(p, stream);
 }
 
-// A ReLU layer that saves z (relu_saves_z): the fp32 instructions, on the
+// A ReLU layer (relu_layer): the fp32 instructions, on the
 // 256x256 tile of 8 waves, the 128x128 one or the 64x64 register-staged one.
-static hipError_t launch_relu_z(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
+static hipError_t launch_relu(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
   if (cfg == kCfg64x64)
     return vec ? launch_f32<true, true, 64, 64, 16, 2, 2, 4, 4, true>(p, stream)
                : launch_f32<true, true, 64, 64, 16, 2, 2, 1, 4, true>(p, stream);
@@ -134,7 +134,7 @@ static hipError_t launch_relu_z(const GemmParams& p, bool vec, int cfg, hipStrea
 }
 
 hipError_t gemm_f32_nt(const GemmParams& p, bool vec, int cfg, hipStream_t stream) {
-  if (relu_saves_z(p)) return launch_relu_z(p, vec, cfg, stream);
+  if (relu_layer(p)) return launch_relu(p, vec, cfg, stream);
   if (p.act || p.z) return launch_epi(p, vec, cfg, stream);
   return launch_layout<true, true>(p, vec, cfg, stream);
 }

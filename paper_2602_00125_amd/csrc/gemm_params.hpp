@@ -112,13 +112,14 @@ struct GemmParams {
   int32_t persist;
 };
 
-// A ReLU layer that saves its pre-activation z for the pullback. Its gradient
-// takes a whole term where z > 0 and none where z <= 0, so a z within rounding
-// of zero turns a term of the gradients on or off when its sum changes order:
-// at 512 x 784 x 1024 about one call in 24 has such a z, and its weight
-// gradient then differs by 9e-4 from the other order's. The sums of such a
-// layer therefore keep one order, that of the fp32 instructions on the tiles
-// choose_epi_cfg names, whatever other products run on.
-inline bool relu_saves_z(const GemmParams& p) { return p.z != nullptr && p.act == 1 /* kActRelu */; }
+// A ReLU layer, whose pullback takes a whole term of the gradients where its
+// pre-activation z > 0 and none where z <= 0: a z within rounding of zero turns
+// a term on or off when its sum changes order. (At 512 x 784 x 1024 about one
+// call in 24 has such a z, and its weight gradient then differs by 9e-4 from
+// the other order's.) The sums of such a layer therefore keep one order, that
+// of the fp32 instructions on the tiles choose_epi_cfg names, whatever other
+// products run on; also where z is not saved, since saving it must not change
+// the outputs.
+inline bool relu_layer(const GemmParams& p) { return p.act == 1 /* kActRelu */; }
 
 }  // namespace mt
