@@ -394,36 +394,54 @@ size_t plan_gemm(GemmCall& g, bool may_split) {
 }
 
 // ---- small products (gemm_small.hpp) or the other tiles: an estimate of each,
-// in us, fitted by least squares to 252 products of 64 to 4096 rows, columns
-// and terms of both types, all layouts, aligned and not (the small tiles
-// within 15% for fp32 and 30% for bf16, the 128x128 ones 13%, 64x64 30%; it
-// only has to rank them).
+// in us, fitted by least squares to the GPU times of 430 layers (16 to 8192
+// rows, 1 to 4096 columns and terms, forward, GELU, dX and dW, both types,
+// aligned and odd, every tile): mean error 5 to 9% for the small and ring
+// tiles, 10 to 12% for 64x64 and 128x128, 23% for bf16 operands without
+// 16-byte rows; they only have to rank the tiles. On those layers the tiles
+// they choose are 2.7% slower than the quickest of all in the mean.
 
-// A small tile's time: a launch, and per round of 256 blocks (one a CU) what a
-// block costs by itself and per K-step of a wave; `vmax` of the slowest block.
+// A block of a small tile and the launch of all: what a block costs by
+// itself, per K-step of a wave (more where both operands are contiguous along
+// k: more lines a load), for K-steps read element by element, a nonlinearity
+// and rows of C without 16-byte groups; 256 blocks at a time, the last round
+// at a share `part` of its fill less.
 struct SmallEst {
-  double launch, block;  // launch; one block
+  double launch, block, part;
   int64_t tiles;
 };
 SmallEst small_est(const GemmCall& g, int cfg) {
   const mt::GemmParams& p = g.p;
-  // launch, block, K-step, K tail (in K-steps: it is read element by element),
-  // and what a K-step costs more when both operands are contiguous along k
-  // (more lines a load), and without 16-byte rows; 64x64 / 32x32 / 16x16
-  static const double f32[3][6] = {{1.6, 5.8, 2.7, 0.5, 1.29, 1.04}, {1.8, 2.9, 1.6, 0.4, 1.21, 1.04},
-                                   {1.7, 2.3, 1.5, 0.3, 1.14, 1.10}};
-  static const double b16[3][6] = {{1.1, 3.2, 1.1, 0.9, 1.5, 1.24}, {1.8, 1.75, 0.65, 1.15, 1.36, 1.26},
-                                   {2.0, 1.8, 0.87, 0.7, 1.0, 1.24}};
-  const int i = cfg - mt::kCfgSmall64;
-  const double* c = g.bf16 ? b16[i] : f32[i];
-  const int64_t t = mt::gemm_tile_m(cfg), waves = cfg == mt::kCfgSmall16 ? 16 : 8;
-  const int64_t tiles = cdiv(p.M, t) * cdiv(p.N, t) * p.keep_count * p.splits;
-  const double step = c[2] * (g.a_kc && g.b_kc ? c[4] : 1.0) * (g.vec ? 1.0 : c[5]);
-  const int64_t whole = p.K / 32 * p.red_count, tails = p.K % 32 ? p.red_count : 0;
-  const double steps = (double)cdiv(cdiv(whole, p.splits), waves) + c[3] * (double)cdiv(cdiv(tails, p.splits), waves);
-  return {c[0], c[1] + steps * step, tiles};
+  // launch, block, K-step, both along k, no 16-byte rows, edge, act, odd C, part; 64x64 / 32x32 / 16x16
+  static const double f32[3][9] = {{2.51, 3.42, 3.13, 0.11, 0.0, 2.2, 1.69, 0.53, 0.14},
+                                   {2.72, 1.71, 1.61, 0.17, 0.01, 1.14, 0.88, 0.14, 0.15},
+                                   {2.63, 1.76, 1.36, 0.02, 0.04, 0.85, 0.69, 0.06, 0.20}};
+  static const double b16[3][9] = {{2.03, 2.6, 1.48, 0.08, 0.03, 1.66, 1.6, 0.61, 0.14},
+                                   {2.63, 1.42, 0.75, 0.10, 0.07, 0.95, 0.92, 0.24, 0.16},
+                                   {2.64, 1.83, 0.72, 0.02, 0.07, 0.61, 0.74, 0.13, 0.25}};
+  const double* c = (g.bf16 ? b16 : f32)[cfg - mt::kCfgSmall64];
+  const int64_t t = mt::gemm_tile_m(cfg), nt = t / 16, waves = cfg == mt::kCfgSmall16 ? 16 : 8;
+  // K-steps of whole vectors, as SmallLoader::whole_steps counts them
+  auto whole = [&](bool kc, int64_t ld, int64_t rows) -> int64_t {
+    if (kc || nt == 1 || rows % t == 0) return p.K / 32;
+    return ld <= 0 ? 0 : std::max<int64_t>(p.K - (ld >= nt ? 1 : cdiv(nt - 1, ld)), 0) / 32;
+  };
+  const int64_t full = std::min(whole(g.a_kc, p.lda, p.M), whole(g.b_kc, p.ldb, p.N));
+  const int64_t edges = cdiv(p.K, 32) - full;
+  const bool nt_layout = g.a_kc && g.b_kc;
+  double block = c[1] + (double)cdiv(full * p.red_count, waves) * c[2] * (nt_layout ? 1.0 + c[3] : 1.0) *
+                            (g.vec ? 1.0 : 1.0 + c[4]);
+  block += (double)cdiv(edges * p.red_count, waves) * c[5] * (nt_layout ? 1.3 : 1.0);
+  if (p.act || p.z) block += c[6];
+  if (p.N % 4 != 0) block += c[7];
+  return {c[0], block, c[8], cdiv(p.M, t) * cdiv(p.N, t) * p.keep_count};
 }
-double small_time(const SmallEst& e) { return e.launch + e.block * (double)cdiv(e.tiles, 256); }
+// `blocks` of 256 at a time, a last round that is part full counted in full but for `part`
+double rounds_of_256(double blocks, double part) {
+  const double full = std::ceil(blocks / 256.0);
+  return full + part * (blocks / 256.0 - full);
+}
+double small_time(const SmallEst& e) { return e.launch + e.block * rounds_of_256((double)e.tiles, e.part); }
 
 // The time of a planned product on the other tiles.
 double ring_time(const GemmCall& g) {
@@ -437,30 +455,44 @@ double ring_time(const GemmCall& g) {
   const bool cut = p.splits > 1;
   if (g.cfg == mt::kCfg64x64) {
     // four blocks a CU, whose stages slow each other down from about 320 on
-    const double slow = std::max(1.0, blocks / 330.0), tail = act * 1.6 * std::ceil(blocks / 1024.0);
+    const double slow = std::max(1.0, blocks / 330.0);
+    double tail = act * 1.6 * std::ceil(blocks / 1024.0);
+    // a saved z beside odd rows of C, element by element: the narrow tiles'
+    // partial lines outgrow the caches (984 x 3270 x 5: 18.5 us without z, 62
+    // with; the 128x128 tile 34 and 37; 1500 x 1501 x 5: 15 and 29)
+    if (p.z && !g.vec && p.M * p.N > 2400000) tail += 10.0 + 10e-6 * (double)(p.M * p.N);
     if (!g.bf16) return 6.4 + stages * 0.458 * (g.vec ? 1.0 : 1.29) * slow + tail + (cut ? 3.0 + 2.8 * mb : 0.0);
     return (g.vec ? 4.8 : 7.9) + stages * (g.vec ? 0.29 : 0.53) * slow + tail + (cut ? 5.5 + mb : 0.0);
   }
-  if (!g.conv && (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8)) {
+  if (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8) {
     if (!g.bf16)
       return 7.5 + rounds * (act * (g.vec ? 7.9 : 20.7) + stages * (g.vec ? 1.43 : 1.65)) + (cut ? 3.0 + 0.75 * mb : 0.0);
     if (g.vec) return 5.9 + rounds * (1.5 + 7.0 * act + stages * 0.53) + (cut ? 1.6 + 0.8 * mb : 0.0);
     return 6.4 + rounds * (7.0 + 11.3 * act) + stages * 1.3 * std::max(1.0, blocks / 550.0) + (cut ? 1.6 + 0.8 * mb : 0.0);
   }
-  // us per stage of one block alone on its CU
-  double per;
+  // launch, block, K-stage, the same without 16-byte rows, act, part, finish, finish a million values
+  struct Est {
+    double launch, block, stage, odd, act, part, fin, fin_mb;
+  };
+  Est e;
   switch (g.cfg) {
-    case mt::kCfgDma256x256: case mt::kCfgDma256x256w4: per = g.bf16 ? 1.8 : 4.8; break;
-    case mt::kCfgDma256x128: case mt::kCfgDma128x256: case mt::kCfg256x128: case mt::kCfg128x256:
-      per = g.bf16 ? 0.6 : 1.4; break;
-    case mt::kCfgDma128x128k64: per = g.bf16 ? 0.6 : 2.9; break;
-    case mt::kCfgDma256x96: case mt::kCfgDma64x384: per = 0.85; break;
-    default: per = g.bf16 ? 0.95 : 1.45; break;
+    case mt::kCfg256x128: case mt::kCfgDma256x128:
+      e = g.bf16 ? Est{7.57, 5.18, 0.52, 4.1, 2.9, 0.35, 0.0, 0.59} : Est{13.7, 0.0, 1.20, 1.38, 3.0, 0.0, 1.56, 0.84};
+      break;
+    case mt::kCfg128x256: case mt::kCfgDma128x256:
+      e = g.bf16 ? Est{6.77, 5.83, 0.40, 4.1, 2.9, 0.14, 0.0, 0.52} : Est{14.4, 0.0, 1.20, 1.39, 3.0, 0.0, 1.38, 0.75};
+      break;
+    case mt::kCfgDma128x128k64:
+      e = g.bf16 ? Est{3.4, 6.99, 0.64, 0.64, 7.6, 0.42, 1.42, 0.94} : Est{2.35, 7.34, 3.45, 3.45, 7.6, 0.21, 1.36, 0.27};
+      break;
+    case mt::kCfgDma256x192: e = {0.0, 13.97, 2.20, 2.20, 0.0, 0.10, 2.75, 0.86}; break;
+    case mt::kCfgDma256x96: e = {12.1, 0.0, 1.25, 1.25, 0.0, 0.0, 3.0, 0.5}; break;
+    case mt::kCfgDma64x384: e = {13.94, 0.0, 1.23, 1.23, 0.0, 0.0, 3.36, 0.35}; break;
+    default:  // 256x256
+      e = g.bf16 ? Est{0.0, 17.0, 1.39, 14.0, 4.9, 0.29, 0.5, 4.4} : Est{0.0, 21.4, 4.37, 5.2, 24.0, 0.10, 2.08, 1.03};
   }
-  if (g.bf16) per *= std::min(1.0, 0.55 + 0.45 * blocks / 256.0);
-  double t = 5.0 + rounds * (4.0 + stages * per * (g.vec ? 1.0 : g.bf16 ? 3.0 : 1.3));
-  if (p.splits > 1) t += 4.0 + (double)(p.splits + 1) * (double)(p.M * p.N * p.keep_count) * 1e-6;
-  return t;
+  return e.launch + (e.block + stages * (g.vec ? e.stage : e.odd) + act * e.act) * rounds_of_256(blocks, e.part) +
+         (cut ? e.fin + e.fin_mb * mb : 0.0);
 }
 
 // Whether the operands' rows keep the small kernel's 32-bit offsets.
@@ -470,15 +502,18 @@ bool small_fits(const GemmCall& g) {
          cdiv(g.p.K, 32) * g.p.red_count < lim / 2 && g.p.keep_count < lim / 2 && g.p.red_count < lim / 2;
 }
 
+// fp32 sums of one or two products take the fp32 instructions: rounded once or
+// twice they are nearer the exact ones than the split's six (K = 1: 2.5e-8 off
+// 64 bits against 3.4e-8; from 3 terms on it is the other way round).
+void mark_shortest_sums(GemmCall& g) { g.p.plain = !g.bf16 && g.p.K * g.p.red_count <= 2; }
+
 // The small tile that should take a planned product instead, or -1.
 int choose_small(const GemmCall& planned, double* time) {
   *time = ring_time(planned);
   int best = -1;
   if (g_force_cfg >= 0 || !small_fits(planned)) return best;
-  GemmCall g = planned;
-  g.p.splits = 1;
   for (int cfg : {mt::kCfgSmall64, mt::kCfgSmall32, mt::kCfgSmall16}) {
-    const double t = small_time(small_est(g, cfg));
+    const double t = small_time(small_est(planned, cfg));
     if (t < 0.95 * *time) {
       *time = t;
       best = cfg;
@@ -487,9 +522,22 @@ int choose_small(const GemmCall& planned, double* time) {
   return best;
 }
 
+// The product as it will run with that workspace on its tile, or `cfg`:
+// without the split where its partial tiles do not fit.
+size_t plan_within(GemmCall& g, int cfg, size_t ws_bytes, bool may_split) {
+  if (cfg >= 0) g.cfg = cfg;
+  const GemmCall asked = g;
+  size_t need = plan_gemm(g, may_split);
+  if (need > ws_bytes && !g.sk) {
+    g = asked;
+    need = plan_gemm(g, false);
+  }
+  return need;
+}
+
 // The tile on which both gradients of a layer run in one launch, or -1: where
 // that is quicker than one launch after the other (each on its best tile).
-int choose_small_bwd(GemmCall& gdx, GemmCall& gdw, bool may_split) {
+int choose_small_bwd(GemmCall& gdx, GemmCall& gdw, size_t ws_bytes, bool may_split) {
   if (!small_fits(gdx) || !small_fits(gdw)) return -1;
   int best = -1;
   if (const int fc = g_force_cfg; fc >= 0) {
@@ -497,18 +545,22 @@ int choose_small_bwd(GemmCall& gdx, GemmCall& gdw, bool may_split) {
     best = fc;
   } else {
     GemmCall x = gdx, w = gdw;
-    plan_gemm(x, may_split);
-    plan_gemm(w, may_split);
+    plan_within(x, -1, ws_bytes, may_split);
+    plan_within(w, -1, ws_bytes, may_split);
     const bool db_apart = gdw.p.colsum && !w.p.colsum;
     double tx, tw;
     choose_small(x, &tx);
     const bool w_small = choose_small(w, &tw) >= 0;
     double least = tx + tw + (db_apart && !w_small ? 5.0 : 0.0);
+    // fitted as above (7 to 10%): the launch, then dX's rounds and after them
+    // dW's (its blocks come last), at least the longer block
+    static const double f32[3][4] = {{2.65, 1.27, 0.89, 0.77}, {4.06, 1.21, 0.84, 0.78}, {1.52, 0.98, 1.02, 1.19}};
+    static const double b16[3][4] = {{2.03, 1.02, 0.88, 0.87}, {2.66, 1.21, 0.96, 0.76}, {1.84, 1.0, 1.01, 1.11}};
     for (int cfg : {mt::kCfgSmall64, mt::kCfgSmall32, mt::kCfgSmall16}) {
-      x.p.splits = w.p.splits = 1;
+      const double* c = (x.bf16 ? b16 : f32)[cfg - mt::kCfgSmall64];
       const SmallEst ex = small_est(x, cfg), ew = small_est(w, cfg);
-      const double all = (ex.block * (double)ex.tiles + ew.block * (double)ew.tiles) / 256.0;
-      const double t = ex.launch + std::max(std::max(ex.block, ew.block), all + 0.5 * std::min(ex.block, ew.block));
+      const double all_x = ex.block * (double)ex.tiles / 256.0, all_w = ew.block * (double)ew.tiles / 256.0;
+      const double t = c[0] + std::max(c[2] * std::max(ex.block, ew.block), c[1] * all_x + c[3] * std::max(ew.block, all_w));
       if (t < least) {
         least = t;
         best = cfg;
@@ -519,6 +571,7 @@ int choose_small_bwd(GemmCall& gdx, GemmCall& gdw, bool may_split) {
   for (GemmCall* g : {&gdx, &gdw}) {
     g->cfg = best;
     plan_gemm(*g, false);
+    mark_shortest_sums(*g);
   }
   return best;
 }
@@ -527,35 +580,38 @@ mt_status launch_gemm(GemmCall& g, hipStream_t stream, void* ws, size_t ws_bytes
   mt::GemmParams& p = g.p;
   if (p.M == 0 || p.N == 0 || p.keep_count == 0) return MT_OK;
   const GemmCall asked = g;
-  size_t need = plan_gemm(g, ws != nullptr);
-  if (need > ws_bytes && !g.sk) {  // as it will run: without the split
-    g = asked;
-    need = plan_gemm(g, false);
-  }
+  size_t need = plan_within(g, -1, ws_bytes, ws != nullptr);
   // (the workspace queries go by the ring tiles' plan, whatever runs)
-  double est;
   if (mt::relu_layer(p)) {
     // one order of its sums: the tile that was asked for
-  } else if (const int small = choose_small(g, &est); small >= 0) {
-    g = asked;
-    g.cfg = small;
-    need = plan_gemm(g, ws != nullptr);
-  } else if (g_force_cfg < 0 && !g.conv && !p.colsum &&
-             (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8)) {
-    // 64x64 tiles where a few 128x128 ones have short contractions (2432 x 832
-    // x 128 with GELU: 22.9 us against 13.5)
+  } else {
+    double est;
+    int small = choose_small(g, &est);
     GemmCall c = asked;
-    c.cfg = mt::kCfg64x64;
-    size_t n = plan_gemm(c, ws != nullptr);
-    if (n > ws_bytes) {
-      c = asked;
-      c.cfg = mt::kCfg64x64;
-      n = plan_gemm(c, false);
+    if (g_force_cfg < 0 && !g.conv && !p.colsum &&
+        (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8 ||
+         g.cfg == mt::kCfgDma128x128k64)) {
+      // 64x64 tiles where a few 128x128 ones have short contractions (2432 x
+      // 832 x 128 with GELU: 22.9 us against 13.5; 8192 x 256 x 16: 13.4
+      // against 7.1)
+      const size_t n = plan_within(c, mt::kCfg64x64, ws_bytes, ws != nullptr);
+      if (ring_time(c) < (small >= 0 ? est : 0.95 * est)) {
+        g = c;
+        need = n;
+        small = -1;
+      }
     }
-    if (ring_time(c) < 0.95 * est) {
-      g = c;
-      need = n;
+    if (small >= 0) {
+      g = asked;
+      g.cfg = small;
+      need = plan_gemm(g, ws != nullptr);
     }
+  }
+  mark_shortest_sums(g);
+  if (p.plain && g_force_cfg < 0 && mt::gemm_tile_m(g.cfg) * mt::gemm_tile_n(g.cfg) > 128 * 128) {
+    g = asked;  // the larger tiles do not heed it
+    need = plan_within(g, mt::kCfgDma128x128, ws_bytes, ws != nullptr);
+    mark_shortest_sums(g);
   }
   if (g.sk && need > ws_bytes) g.sk = 0;  // no room for the partial tiles: one tile per block
   if (g.sk) {
@@ -756,7 +812,7 @@ mt_status linear_bwd_impl(const mt_tensor* x, const mt_tensor* w, const mt_tenso
   fold_db = false;
   if (dx && dw && M > 0 && N > 0 && K > 0) {
     // both gradients of a small layer (and db) in one launch
-    if (const int cfg = choose_small_bwd(gdx, gdw, ws != nullptr); cfg >= 0) {
+    if (const int cfg = choose_small_bwd(gdx, gdw, ws_bytes, ws != nullptr); cfg >= 0) {
       (void)hipGetLastError();
       return hip_status(bf ? mt::gemm_small_bwd_bf16(gdx.p, gdw.p, cfg, stream)
                            : mt::gemm_small_bwd_f32(gdx.p, gdw.p, cfg, stream));

@@ -110,6 +110,10 @@ struct GemmParams {
   // the size of a persistent grid (one block per CU, each walking the tiles
   // of the plain grid's blocks b, b + persist, ...); 0: the plain grid
   int32_t persist;
+  // fp32 operands, small tiles and ring tiles of up to 128x128: every tile by
+  // the fp32 instructions (what a tile otherwise takes only where its results
+  // are not finite)
+  int32_t plain;
 };
 
 // A ReLU layer, whose pullback takes a whole term of the gradients where its

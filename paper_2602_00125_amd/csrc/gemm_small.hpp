@@ -341,16 +341,17 @@ struct SmallGemm {
       return z != z;
     };
     auto multiply = [&](auto plain, const typename Op::Raw (&xa)[TM], const typename Op::Raw (&xb)[TN]) {
+      if constexpr (!A_KC) {
+        // (the second pass of a share: the first has summed them)
+        if (cs_on && (!decltype(plain)::value || p.plain)) {
+#pragma unroll
+          for (int i = 0; i < TM; ++i) cs[i] += Op::sum(xa[i]);
+        }
+      }
       if constexpr (decltype(plain)::value) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) std::conditional_t<decltype(plain)::value, Op, void>::plain(xa[i], xb, acc[i]);
       } else {
-        if constexpr (!A_KC) {
-          if (cs_on) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) cs[i] += Op::sum(xa[i]);
-          }
-        }
         typename Op::Frag fb[TN];
 #pragma unroll
         for (int q = 0; q < TN; ++q) fb[q] = Op::frag(xb[q], b_scale);
@@ -456,7 +457,8 @@ struct SmallGemm {
       deposit(deposited, unscale);
       return bad;
     };
-    const bool bad = take_share(std::false_type{});
+    bool bad = true;
+    if (!Op::SPLIT || !p.plain) bad = take_share(std::false_type{});
     if constexpr (Op::SPLIT) {
       // what the split does not serve: the share again, by the fp32
       // instructions (16 x 4096 x 4096 forward 23.4 us, with one NaN in x

@@ -268,3 +268,35 @@ def test_refused_values_through_every_epilogue(cfg, vec1, kind):
     finally:
         for k, v in (("cfg", -1), ("vec1", 0), ("splits", 0)):
             b.debug_set(k, v)
+
+
+@pytest.mark.parametrize("cfg", [-1, 4, 10, 12, 16, 18])
+@pytest.mark.parametrize("M,N", [(300, 200), (4352, 4096)])  # the second would be planned on 256x256 tiles
+def test_sums_of_one_or_two_products_are_rounded_as_such(cfg, M, N):
+    """K = 1 is the rounded product itself, K = 2 the fused multiply-add of the second."""
+    if cfg in (16, 18) and M > 300:
+        pytest.skip("small tiles")
+    g = torch.Generator().manual_seed(M)
+    for K in (1, 2):
+        x, w = torch.randn(M, 4, generator=g), torch.randn(N, 4, generator=g)
+        xd, wd = x.to(DEV)[:, :K], w.to(DEV)[:, :K]
+        y = torch.full((M, N), math.nan, device=DEV)
+        try:
+            b.debug_set("cfg", cfg)
+            b.linear_fwd(xd, wd, None, y)
+        finally:
+            b.debug_set("cfg", -1)
+        want = (xd[:, :1].double() * wd[:, 0].double()).float()
+        dw, db = torch.full((M, N), math.nan, device=DEV), torch.full((M,), math.nan, device=DEV)
+        try:  # the same as a TN product with the column sums of its first operand
+            b.debug_set("cfg", cfg)
+            b.linear_bwd(wd.t().contiguous(), None, xd.t().contiguous(), None, dw, db)
+        finally:
+            b.debug_set("cfg", -1)
+        assert torch.equal(dw, y)
+        assert float((db.double() - xd.double().sum(1)).abs().max()) <= 2.0 ** -22
+        if K == 2:  # (a sum of 48-bit products in 64 bits, rounded again: off by one place in 2^28)
+            want = (xd[:, 1:2].double() * wd[:, 1].double() + want.double()).float()
+            assert float((y != want).float().mean()) < 1e-6
+        else:
+            assert torch.equal(y, want)
