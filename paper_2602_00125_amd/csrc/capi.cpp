@@ -379,7 +379,7 @@ size_t plan_gemm(GemmCall& g, bool may_split) {
   // a convolution's weight gradient is few tiles over every output pixel
   // (16 x 64 x 28 x 28 outputs, 128 3x3 filters: 5 tiles over 12544, 16 runs on
   // 80 blocks 57 us): as many runs of 8 stages as fill the chip
-  const int want = choose_splits(blocks, stages, g.cfg, g.conv == 2 ? 128 : 16);
+  const int want = choose_splits(blocks, stages, g.cfg, g.runs > 0 ? g.runs : g.conv == 2 ? 128 : 16);
   if (want <= 1) return 0;
   const int64_t per = cdiv(stages, want);
   const int64_t splits = cdiv(stages, per);
@@ -522,12 +522,20 @@ int choose_small(const GemmCall& planned, double* time) {
   return best;
 }
 
-// The product as it will run with that workspace on its tile, or `cfg`:
-// without the split where its partial tiles do not fit.
+// The product as it will run with that workspace on its tile, or `cfg`: a
+// weight gradient of a convolution in as many runs as fit, down to 16 (others
+// take no more); without the split where the partial tiles do not fit.
 size_t plan_within(GemmCall& g, int cfg, size_t ws_bytes, bool may_split) {
+  const mt::GemmParams& p = g.p;
   if (cfg >= 0) g.cfg = cfg;
   const GemmCall asked = g;
   size_t need = plan_gemm(g, may_split);
+  if (need > ws_bytes && g.conv == 2 && p.splits > 16) {
+    const int fit = (int)std::max<size_t>(16, ws_bytes / (need / p.splits + 1));
+    g = asked;
+    g.runs = fit;
+    need = plan_gemm(g, may_split);
+  }
   if (need > ws_bytes && !g.sk) {
     g = asked;
     need = plan_gemm(g, false);

@@ -40,6 +40,7 @@ struct GemmCall {
   int cfg;
   int conv;   // 1 / 2 / 3: the convolution product gathering an operand (p.cg), else 0
   int sk;     // stream-K blocks (conv 1 and 3 on the 256x256 tile), else 0
+  int runs;   // most split-K runs (0: as many as the kind of product takes)
 };
 
 

@@ -185,6 +185,28 @@ def test_runs_of_a_long_contraction():
         close(db, D.sum(0), D.abs().sum(0), 20000, "db")
 
 
+def test_convolution_weight_gradient_within_a_smaller_workspace():
+    """49 runs where the workspace holds them; fewer, down to 16, where it does
+    not (whole, it takes 18 times as long)."""
+    N, C, H, W, CO = 16, 64, 56, 56, 128
+    x, w, dy = (torch.randn(s, device=DEV).contiguous(memory_format=torch.channels_last)
+                for s in ((N, C, H, W), (CO, C, 3, 3), (N, CO, 28, 28)))
+    dw, db = torch.empty_like(w), torch.empty(CO, device=DEV)
+    full = b.conv2d_bwd_workspace(x, w, dy, None, dw, db, 2, 1)
+    X, K = x.double().cpu(), w.double().cpu().requires_grad_()
+    out = torch.nn.functional.conv2d(X, K, stride=2, padding=1)
+    want, = torch.autograd.grad(out, K, dy.double().cpu())
+    S, = torch.autograd.grad(torch.nn.functional.conv2d(X.abs(), K, stride=2, padding=1), K, dy.double().cpu().abs())
+    t = []
+    for n in (full, full // 3):
+        ws = torch.empty(n, dtype=torch.uint8, device=DEV)
+        dw.fill_(math.nan), db.fill_(math.nan)
+        t.append(best_time(lambda: b.conv2d_bwd(x, w, dy, None, dw, db, 2, 1, workspace=ws)))
+        close(dw, want, S, N * 28 * 28, f"dw in {n} bytes")
+        close(db, dy.double().cpu().sum((0, 2, 3)), dy.double().cpu().abs().sum((0, 2, 3)), N * 28 * 28, f"db in {n} bytes")
+    assert t[1] < 4 * t[0], t
+
+
 # outputs and sums around every group size (4, 16, 64 and 256 lanes), with
 # and without 16-byte rows, one and several summed axes, views
 REDUCTIONS = [((3, 5, 7), k) for k in ("a", "b", "c", "ab", "ac", "bc", "")] + \
