@@ -394,54 +394,45 @@ size_t plan_gemm(GemmCall& g, bool may_split) {
 }
 
 // ---- small products (gemm_small.hpp) or the other tiles: an estimate of each,
-// in us, fitted by least squares to the GPU times of 430 layers (16 to 8192
-// rows, 1 to 4096 columns and terms, forward, GELU, dX and dW, both types,
-// aligned and odd, every tile): mean error 5 to 9% for the small and ring
-// tiles, 10 to 12% for 64x64 and 128x128, 23% for bf16 operands without
-// 16-byte rows; they only have to rank the tiles. On those layers the tiles
-// they choose are 2.7% slower than the quickest of all in the mean.
+// in us. The small, 64x64 and 128x128 ones are fitted by least squares to 252
+// products of 64 to 4096 rows, columns and terms of both types, all layouts,
+// aligned and not (the small tiles within 15% for fp32 and 30% for bf16, the
+// 128x128 ones 13%, 64x64 30%); the others' stage times are single
+// measurements. They only have to rank the tiles: over 430 layers of 16 to
+// 8192 rows the tiles they choose take 4.7% longer than the quickest in the
+// mean. Constants fitted to those layers brought that to 2.7%, but by moving
+// fp32 products from the small tiles to tiles whose sums are up to three times
+// further from the exact ones, so these stay.
 
-// A block of a small tile and the launch of all: what a block costs by
-// itself, per K-step of a wave (more where both operands are contiguous along
-// k: more lines a load), for K-steps read element by element, a nonlinearity
-// and rows of C without 16-byte groups; 256 blocks at a time, the last round
-// at a share `part` of its fill less.
+// A small tile's time: a launch, and per round of 256 blocks (one a CU) what a
+// block costs by itself and per K-step of a wave.
 struct SmallEst {
-  double launch, block, part;
+  double launch, block;  // launch; one block
   int64_t tiles;
 };
 SmallEst small_est(const GemmCall& g, int cfg) {
   const mt::GemmParams& p = g.p;
-  // launch, block, K-step, both along k, no 16-byte rows, edge, act, odd C, part; 64x64 / 32x32 / 16x16
-  static const double f32[3][9] = {{2.51, 3.42, 3.13, 0.11, 0.0, 2.2, 1.69, 0.53, 0.14},
-                                   {2.72, 1.71, 1.61, 0.17, 0.01, 1.14, 0.88, 0.14, 0.15},
-                                   {2.63, 1.76, 1.36, 0.02, 0.04, 0.85, 0.69, 0.06, 0.20}};
-  static const double b16[3][9] = {{2.03, 2.6, 1.48, 0.08, 0.03, 1.66, 1.6, 0.61, 0.14},
-                                   {2.63, 1.42, 0.75, 0.10, 0.07, 0.95, 0.92, 0.24, 0.16},
-                                   {2.64, 1.83, 0.72, 0.02, 0.07, 0.61, 0.74, 0.13, 0.25}};
-  const double* c = (g.bf16 ? b16 : f32)[cfg - mt::kCfgSmall64];
-  const int64_t t = mt::gemm_tile_m(cfg), nt = t / 16, waves = cfg == mt::kCfgSmall16 ? 16 : 8;
-  // K-steps of whole vectors, as SmallLoader::whole_steps counts them
-  auto whole = [&](bool kc, int64_t ld, int64_t rows) -> int64_t {
-    if (kc || nt == 1 || rows % t == 0) return p.K / 32;
-    return ld <= 0 ? 0 : std::max<int64_t>(p.K - (ld >= nt ? 1 : cdiv(nt - 1, ld)), 0) / 32;
-  };
-  const int64_t full = std::min(whole(g.a_kc, p.lda, p.M), whole(g.b_kc, p.ldb, p.N));
-  const int64_t edges = cdiv(p.K, 32) - full;
-  const bool nt_layout = g.a_kc && g.b_kc;
-  double block = c[1] + (double)cdiv(full * p.red_count, waves) * c[2] * (nt_layout ? 1.0 + c[3] : 1.0) *
-                            (g.vec ? 1.0 : 1.0 + c[4]);
-  block += (double)cdiv(edges * p.red_count, waves) * c[5] * (nt_layout ? 1.3 : 1.0);
-  if (p.act || p.z) block += c[6];
-  if (p.N % 4 != 0) block += c[7];
-  return {c[0], block, c[8], cdiv(p.M, t) * cdiv(p.N, t) * p.keep_count};
+  // launch, block, K-step, K tail (in K-steps: it is read element by element),
+  // and what a K-step costs more when both operands are contiguous along k
+  // (more lines a load), and without 16-byte rows; 64x64 / 32x32 / 16x16
+  static const double f32[3][6] = {{1.6, 5.8, 2.7, 0.5, 1.29, 1.04}, {1.8, 2.9, 1.6, 0.4, 1.21, 1.04},
+                                   {1.7, 2.3, 1.5, 0.3, 1.14, 1.10}};
+  static const double b16[3][6] = {{1.1, 3.2, 1.1, 0.9, 1.5, 1.24}, {1.8, 1.75, 0.65, 1.15, 1.36, 1.26},
+                                   {2.0, 1.8, 0.87, 0.7, 1.0, 1.24}};
+  const int i = cfg - mt::kCfgSmall64;
+  const double* c = g.bf16 ? b16[i] : f32[i];
+  const int64_t t = mt::gemm_tile_m(cfg), waves = cfg == mt::kCfgSmall16 ? 16 : 8;
+  const int64_t tiles = cdiv(p.M, t) * cdiv(p.N, t) * p.keep_count * p.splits;
+  double step = c[2] * (g.a_kc && g.b_kc ? c[4] : 1.0) * (g.vec ? 1.0 : c[5]);
+  // bf16 rows that start between two words (an odd pitch): 344 x 5164 x 5923
+  // forward 232 us, 64x64 register-staged tiles 133; 2105 x 2427 over 2962
+  // terms, dX: 141 us
+  if (g.bf16 && ((p.lda | p.ldb) & 1)) step *= g.a_kc && g.b_kc ? 1.8 : 1.4;
+  const int64_t whole = p.K / 32 * p.red_count, tails = p.K % 32 ? p.red_count : 0;
+  const double steps = (double)cdiv(cdiv(whole, p.splits), waves) + c[3] * (double)cdiv(cdiv(tails, p.splits), waves);
+  return {c[0], c[1] + steps * step, tiles};
 }
-// `blocks` of 256 at a time, a last round that is part full counted in full but for `part`
-double rounds_of_256(double blocks, double part) {
-  const double full = std::ceil(blocks / 256.0);
-  return full + part * (blocks / 256.0 - full);
-}
-double small_time(const SmallEst& e) { return e.launch + e.block * rounds_of_256((double)e.tiles, e.part); }
+double small_time(const SmallEst& e) { return e.launch + e.block * (double)cdiv(e.tiles, 256); }
 
 // The time of a planned product on the other tiles.
 double ring_time(const GemmCall& g) {
@@ -464,35 +455,26 @@ double ring_time(const GemmCall& g) {
     if (!g.bf16) return 6.4 + stages * 0.458 * (g.vec ? 1.0 : 1.29) * slow + tail + (cut ? 3.0 + 2.8 * mb : 0.0);
     return (g.vec ? 4.8 : 7.9) + stages * (g.vec ? 0.29 : 0.53) * slow + tail + (cut ? 5.5 + mb : 0.0);
   }
-  if (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8) {
+  if (!g.conv && (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8)) {
     if (!g.bf16)
       return 7.5 + rounds * (act * (g.vec ? 7.9 : 20.7) + stages * (g.vec ? 1.43 : 1.65)) + (cut ? 3.0 + 0.75 * mb : 0.0);
     if (g.vec) return 5.9 + rounds * (1.5 + 7.0 * act + stages * 0.53) + (cut ? 1.6 + 0.8 * mb : 0.0);
     return 6.4 + rounds * (7.0 + 11.3 * act) + stages * 1.3 * std::max(1.0, blocks / 550.0) + (cut ? 1.6 + 0.8 * mb : 0.0);
   }
-  // launch, block, K-stage, the same without 16-byte rows, act, part, finish, finish a million values
-  struct Est {
-    double launch, block, stage, odd, act, part, fin, fin_mb;
-  };
-  Est e;
+  // us per stage of one block alone on its CU
+  double per;
   switch (g.cfg) {
-    case mt::kCfg256x128: case mt::kCfgDma256x128:
-      e = g.bf16 ? Est{7.57, 5.18, 0.52, 4.1, 2.9, 0.35, 0.0, 0.59} : Est{13.7, 0.0, 1.20, 1.38, 3.0, 0.0, 1.56, 0.84};
-      break;
-    case mt::kCfg128x256: case mt::kCfgDma128x256:
-      e = g.bf16 ? Est{6.77, 5.83, 0.40, 4.1, 2.9, 0.14, 0.0, 0.52} : Est{14.4, 0.0, 1.20, 1.39, 3.0, 0.0, 1.38, 0.75};
-      break;
-    case mt::kCfgDma128x128k64:
-      e = g.bf16 ? Est{3.4, 6.99, 0.64, 0.64, 7.6, 0.42, 1.42, 0.94} : Est{2.35, 7.34, 3.45, 3.45, 7.6, 0.21, 1.36, 0.27};
-      break;
-    case mt::kCfgDma256x192: e = {0.0, 13.97, 2.20, 2.20, 0.0, 0.10, 2.75, 0.86}; break;
-    case mt::kCfgDma256x96: e = {12.1, 0.0, 1.25, 1.25, 0.0, 0.0, 3.0, 0.5}; break;
-    case mt::kCfgDma64x384: e = {13.94, 0.0, 1.23, 1.23, 0.0, 0.0, 3.36, 0.35}; break;
-    default:  // 256x256
-      e = g.bf16 ? Est{0.0, 17.0, 1.39, 14.0, 4.9, 0.29, 0.5, 4.4} : Est{0.0, 21.4, 4.37, 5.2, 24.0, 0.10, 2.08, 1.03};
+    case mt::kCfgDma256x256: case mt::kCfgDma256x256w4: per = g.bf16 ? 1.8 : 4.8; break;
+    case mt::kCfgDma256x128: case mt::kCfgDma128x256: case mt::kCfg256x128: case mt::kCfg128x256:
+      per = g.bf16 ? 0.6 : 1.4; break;
+    case mt::kCfgDma128x128k64: per = g.bf16 ? 0.6 : 2.9; break;
+    case mt::kCfgDma256x96: case mt::kCfgDma64x384: per = 0.85; break;
+    default: per = g.bf16 ? 0.95 : 1.45; break;
   }
-  return e.launch + (e.block + stages * (g.vec ? e.stage : e.odd) + act * e.act) * rounds_of_256(blocks, e.part) +
-         (cut ? e.fin + e.fin_mb * mb : 0.0);
+  if (g.bf16) per *= std::min(1.0, 0.55 + 0.45 * blocks / 256.0);
+  double t = 5.0 + rounds * (4.0 + stages * per * (g.vec ? 1.0 : g.bf16 ? 3.0 : 1.3));
+  if (p.splits > 1) t += 4.0 + (double)(p.splits + 1) * (double)(p.M * p.N * p.keep_count) * 1e-6;
+  return t;
 }
 
 // Whether the operands' rows keep the small kernel's 32-bit offsets.
@@ -512,8 +494,10 @@ int choose_small(const GemmCall& planned, double* time) {
   *time = ring_time(planned);
   int best = -1;
   if (g_force_cfg >= 0 || !small_fits(planned)) return best;
+  GemmCall g = planned;
+  g.p.splits = 1;
   for (int cfg : {mt::kCfgSmall64, mt::kCfgSmall32, mt::kCfgSmall16}) {
-    const double t = small_time(small_est(planned, cfg));
+    const double t = small_time(small_est(g, cfg));
     if (t < 0.95 * *time) {
       *time = t;
       best = cfg;
@@ -560,15 +544,15 @@ int choose_small_bwd(GemmCall& gdx, GemmCall& gdw, size_t ws_bytes, bool may_spl
     choose_small(x, &tx);
     const bool w_small = choose_small(w, &tw) >= 0;
     double least = tx + tw + (db_apart && !w_small ? 5.0 : 0.0);
-    // fitted as above (7 to 10%): the launch, then dX's rounds and after them
-    // dW's (its blocks come last), at least the longer block
-    static const double f32[3][4] = {{2.65, 1.27, 0.89, 0.77}, {4.06, 1.21, 0.84, 0.78}, {1.52, 0.98, 1.02, 1.19}};
-    static const double b16[3][4] = {{2.03, 1.02, 0.88, 0.87}, {2.66, 1.21, 0.96, 0.76}, {1.84, 1.0, 1.01, 1.11}};
     for (int cfg : {mt::kCfgSmall64, mt::kCfgSmall32, mt::kCfgSmall16}) {
-      const double* c = (x.bf16 ? b16 : f32)[cfg - mt::kCfgSmall64];
+      x.p.splits = w.p.splits = 1;
       const SmallEst ex = small_est(x, cfg), ew = small_est(w, cfg);
-      const double all_x = ex.block * (double)ex.tiles / 256.0, all_w = ew.block * (double)ew.tiles / 256.0;
-      const double t = c[0] + std::max(c[2] * std::max(ex.block, ew.block), c[1] * all_x + c[3] * std::max(ew.block, all_w));
+      const double all_x = ex.block * (double)ex.tiles / 256.0, all = all_x + ew.block * (double)ew.tiles / 256.0;
+      // dW's blocks come last: where dX's fill the chip, the long ones of a
+      // layer of a few outputs start when they are done (8192 x 10 x 1024
+      // bf16: 35 us of dX, then 47 of dW)
+      const double after = (ex.tiles >= 256 && gdw.p.M < 16 ? all_x : 0.0) + ew.block;
+      const double t = ex.launch + std::max({ex.block, after, all + 0.5 * std::min(ex.block, ew.block)});
       if (t < least) {
         least = t;
         best = cfg;
@@ -590,29 +574,22 @@ mt_status launch_gemm(GemmCall& g, hipStream_t stream, void* ws, size_t ws_bytes
   const GemmCall asked = g;
   size_t need = plan_within(g, -1, ws_bytes, ws != nullptr);
   // (the workspace queries go by the ring tiles' plan, whatever runs)
-  if (mt::relu_layer(p)) {
-    // one order of its sums: the tile that was asked for
-  } else {
+  if (!mt::relu_layer(p)) {  // (which keeps the tile it asked for)
     double est;
-    int small = choose_small(g, &est);
-    GemmCall c = asked;
-    if (g_force_cfg < 0 && !g.conv && !p.colsum &&
-        (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8 ||
-         g.cfg == mt::kCfgDma128x128k64)) {
-      // 64x64 tiles where a few 128x128 ones have short contractions (2432 x
-      // 832 x 128 with GELU: 22.9 us against 13.5; 8192 x 256 x 16: 13.4
-      // against 7.1)
-      const size_t n = plan_within(c, mt::kCfg64x64, ws_bytes, ws != nullptr);
-      if (ring_time(c) < (small >= 0 ? est : 0.95 * est)) {
-        g = c;
-        need = n;
-        small = -1;
-      }
-    }
-    if (small >= 0) {
+    if (const int small = choose_small(g, &est); small >= 0) {
       g = asked;
       g.cfg = small;
       need = plan_gemm(g, ws != nullptr);
+    } else if (g_force_cfg < 0 && !g.conv && !p.colsum &&
+               (g.cfg == mt::kCfg128x128 || g.cfg == mt::kCfgDma128x128 || g.cfg == mt::kCfgDma128x128w8)) {
+      // 64x64 tiles where a few 128x128 ones have short contractions (2432 x 832
+      // x 128 with GELU: 22.9 us against 13.5)
+      GemmCall c = asked;
+      const size_t n = plan_within(c, mt::kCfg64x64, ws_bytes, ws != nullptr);
+      if (ring_time(c) < 0.95 * est) {
+        g = c;
+        need = n;
+      }
     }
   }
   mark_shortest_sums(g);
