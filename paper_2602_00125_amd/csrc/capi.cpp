@@ -238,9 +238,9 @@ int choose_splits(int64_t blocks, int64_t stages, int cfg, int64_t most) {
 }
 
 // Tiles that carry the dense-layer-with-nonlinearity epilogue: the 256x256
-// DMA tile for large products, else the 128x128 DMA tile (register-staged
-// for unaligned operands) or 64x64 (a forced cfg outside these maps to the
-// nearest of them).
+// DMA tile for large products, else 128x128 (the DMA tile; register-staged for
+// bf16 operands and ReLU layers without 16-byte rows) or 64x64 (a forced cfg
+// outside these maps to the nearest of them).
 int choose_epi_cfg(int64_t M, int64_t N, bool vec) {
   auto tiles = [&](int64_t bm, int64_t bn) { return cdiv(M, bm) * cdiv(N, bn); };
   if (const int fc = g_force_cfg; fc >= 0) {
