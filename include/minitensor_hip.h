@@ -39,7 +39,9 @@
  *     bf16 parts (six v_mfma_f32_32x32x16_bf16 per 16 terms; products below
  *     2^-24 of a term are left out). Tiles whose results are not finite that
  *     way (infinities, NaN, values from 2^104 and sums from 2^80 on) are
- *     computed by v_mfma_f32_32x32x2_f32 instead. bf16 operands are multiplied
+ *     computed by v_mfma_f32_32x32x2_f32 instead, as are sums of one or two
+ *     terms and ReLU layers (mt_linear_act_fwd), whose gradients turn on the
+ *     sign of a sum. bf16 operands are multiplied
  *     exactly and accumulated in fp32 (v_mfma_f32_32x32x16_bf16). Every
  *     output, bias and bias gradient is fp32.
  */

@@ -487,7 +487,10 @@ bool small_fits(const GemmCall& g) {
 // fp32 sums of one or two products take the fp32 instructions: rounded once or
 // twice they are nearer the exact ones than the split's six (K = 1: 2.5e-8 off
 // 64 bits against 3.4e-8; from 3 terms on it is the other way round).
-void mark_shortest_sums(GemmCall& g) { g.p.plain = !g.bf16 && g.p.K * g.p.red_count <= 2; }
+void mark_shortest_sums(GemmCall& g) {
+  const int64_t terms = g.p.K * g.p.red_count;
+  g.p.plain = !g.bf16 && terms > 0 && terms <= 2;
+}
 
 // The small tile that should take a planned product instead, or -1.
 int choose_small(const GemmCall& planned, double* time) {

@@ -300,3 +300,30 @@ def test_sums_of_one_or_two_products_are_rounded_as_such(cfg, M, N):
             assert float((y != want).float().mean()) < 1e-6
         else:
             assert torch.equal(y, want)
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_weight_gradient_of_a_convolution_over_one_or_two_pixels(n):
+    g = torch.Generator().manual_seed(n)
+    cl = torch.channels_last
+    x, w, dy = (torch.randn(s, generator=g).to(DEV).contiguous(memory_format=cl)
+                for s in ((n, 64, 3, 3), (96, 64, 3, 3), (n, 96, 1, 1)))
+    dw, db = torch.full_like(w, math.nan), torch.full((96,), math.nan, device=DEV)
+    ws = torch.empty(max(1, b.conv2d_bwd_workspace(x, w, dy, None, dw, db)), dtype=torch.uint8, device=DEV)
+    b.conv2d_bwd(x, w, dy, None, dw, db, workspace=ws)
+    X, D = x.double().cpu(), dy.double().cpu().view(n, 96)
+    want = torch.einsum("no,nchw->ochw", D, X)
+    check(dw, want, torch.einsum("no,nchw->ochw", D.abs(), X.abs()), n, "dw")
+    check(db, D.sum(0), D.abs().sum(0), n, "db")
+
+
+@pytest.mark.parametrize("shape", [((0, 5, 0), (0, 7)), ((3, 5, 0), (0, 7))])
+def test_empty_contractions_are_zero(shape):
+    """(no term: neither the split nor the fp32 instructions have a stage)"""
+    a, k = torch.empty(shape[0], device=DEV), torch.empty(shape[1], device=DEV)
+    c = torch.full((*shape[0][:2], 7), math.nan, device=DEV)
+    b.matmul(a, k, c)
+    assert bool((c == 0).all())
+    r = torch.full((1, 5, 7), math.nan, device=DEV)  # summed over the batch axis, empty or not
+    b.matmul(torch.empty(shape[0][0], 5, 4, device=DEV).zero_(), torch.ones(shape[0][0], 4, 7, device=DEV), r, reduce_into=True)
+    assert bool((r == 0).all())
