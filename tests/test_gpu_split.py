@@ -270,12 +270,11 @@ def test_refused_values_through_every_epilogue(cfg, vec1, kind):
             b.debug_set(k, v)
 
 
-@pytest.mark.parametrize("cfg", [-1, 4, 10, 12, 16, 18])
-@pytest.mark.parametrize("M,N", [(300, 200), (4352, 4096)])  # the second would be planned on 256x256 tiles
+# (the larger ones would be planned on 256x256 tiles)
+@pytest.mark.parametrize("cfg,M,N", [(c, 300, 200) for c in (-1, 4, 10, 12, 16, 18)] +
+                         [(c, 4352, 4096) for c in (-1, 4, 10, 12)])
 def test_sums_of_one_or_two_products_are_rounded_as_such(cfg, M, N):
     """K = 1 is the rounded product itself, K = 2 the fused multiply-add of the second."""
-    if cfg in (16, 18) and M > 300:
-        pytest.skip("small tiles")
     g = torch.Generator().manual_seed(M)
     for K in (1, 2):
         x, w = torch.randn(M, 4, generator=g), torch.randn(N, 4, generator=g)
