@@ -169,7 +169,7 @@ def test_layers_of_a_few_outputs(N, dtype):
         return best_time(lambda: b.linear_bwd(x, w, dy, *o, workspace=ws))
 
     # one wave walking 256 K-steps alone took 7 times as long as 64 outputs
-    assert step(N) < 2 * step(64)
+    assert step(N) < 3 * step(64)
 
 
 def test_runs_of_a_long_contraction():
